@@ -1,6 +1,7 @@
 // C-ABI entry points: argument validation, workspace planning and launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <map>
@@ -327,10 +328,28 @@ void apply_march_opts(KArgs& k, const nedf_march_opts& o) {
 // Plain-marcher depth into k.depth / k.id / k.opacity.
 void run_march(const Prepared& P, int dtype, hipStream_t s) {
   stage_init_cull(P.k, s, P.mlp, march_waves(dtype, P.W));
-  KArgs k = P.k;
-  k.L = &k.C->A;
-  stage_march(k, s, false, P.analytic, dtype, P.mlp ? P.W : 0, P.H, P.L);
+  stage_march(P.k, s, false, P.analytic, dtype, P.mlp ? P.W : 0, P.H, P.L);
   stage_finalize(P.k, s);
+}
+
+// Depth slabs of the network stage.  Each slab beyond the first costs a filter
+// and a launch (about 10 us, and the chip empties at the end of each) and
+// saves the pairs hidden behind the slabs before it, which takes several
+// objects along a ray and more pairs than a few rounds of the chip.  Culling
+// keeps about a tenth of rays x instances, and a round takes 65,536 pairs, so
+// one slab per 4 M rays x instances leaves a slab several rounds: measured
+// on one box, 1 slab against 8: 64 x 64, 8 instances, 0.45 / 0.71 ms; 20,011
+// FP32 rays, 24 instances, 2.7 / 4.3 ms; 32 against 8: 1080p, 1,000
+// instances, 25.5 / 32.0 ms; 2 against 8: classifier, 900 x 600, 20
+// instances, 6.0 / 6.5 ms.  A value set in the tuning table is taken as it is.
+int depth_slabs(const KArgs& k, int dtype) {
+  const int dt = dtype == NEDF_FP8_MX ? NEDF_FP8 : dtype;  // MX networks take the FP8 entry
+  const int v = tune_value(NEDF_TUNE_SLABS, dt);
+  if (v != NEDF_SLABS_DEFAULT) return v;
+  const int64_t most = std::min<int64_t>(k.capacity, k.n_rays * k.n_inst);
+  int s = 1;
+  while (s < 32 && 2 * s <= k.n_inst && most >= int64_t(2 * s) << 22) s *= 2;
+  return s;
 }
 
 // NeDF depth keys (+ fallback) of every pair into k.keys.
@@ -339,13 +358,11 @@ void run_infer_keys(const Prepared& P, int dtype, const nedf_infer_opts& o, hipS
   k.p_lo = o.p_lo;
   k.p_hi = o.p_hi;
   stage_init_cull(k, s, P.nedf, 32 * eng::WAVES);
-  k.L = &k.C->A;
   // analytic objects without a network are marched directly
   const uint32_t direct = P.analytic & ~P.nedf;
   if (direct) stage_march(k, s, false, direct, dtype, 0, 0, 0);
-  // MX networks take the FP8 slab count
-  const int slab_dt = P.nedf_dtype == NEDF_FP8_MX ? NEDF_FP8 : P.nedf_dtype;
-  if (P.nedf) stage_nedf(k, s, P.nedf_dtype, P.nedf, tune_value(NEDF_TUNE_SLABS, slab_dt), P.nedf_cls);
+  if (!P.nedf) return;
+  stage_nedf(k, s, P.nedf_dtype, P.nedf, depth_slabs(k, P.nedf_dtype), P.nedf_cls);
   // uncertain pairs: marcher on list B
   stage_march(k, s, true, P.analytic, dtype, (P.mlp & P.nedf) ? P.W : 0, P.H, P.L);
 }
@@ -353,12 +370,14 @@ void run_infer_keys(const Prepared& P, int dtype, const nedf_infer_opts& o, hipS
 // Keys -> depth / id, then refinement of the winners.
 void run_finish(const Prepared& P, int dtype, const nedf_infer_opts& o, hipStream_t s) {
   KArgs k = P.k;
-  stage_finalize(k, s);
-  if (o.refine_steps > 0 && k.id) {
+  const bool refine = o.refine_steps > 0 && k.id;
+  const uint32_t mlp_ok = refine && refine_supported(dtype, P.dshape) ? P.sdf_mlp : 0u;
+  const uint32_t sphere = refine ? P.sphere : 0u;
+  stage_finalize(k, s, mlp_ok | sphere);
+  if (mlp_ok | sphere) {
     k.refine_h = o.refine_h;
     k.refine_steps = o.refine_steps;
-    const uint32_t mlp_ok = refine_supported(dtype, P.dshape) ? P.sdf_mlp : 0u;
-    if (mlp_ok | P.sphere) stage_refine(k, s, k.id, mlp_ok, P.sphere, dtype);
+    stage_refine(k, s, k.id, mlp_ok, sphere, dtype);
   }
 }
 
@@ -436,8 +455,8 @@ extern "C" int32_t nedf_ws_counters(const void* ws, nedf_stream_t stream, int64_
   WsCounters c;
   e = hipMemcpy(&c, static_cast<const uint8_t*>(ws) + 256, sizeof(c), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return hip_fail(e, "nedf_ws_counters");
-  out7[0] = c.A.total_pairs;
-  out7[1] = c.A.total_items;
+  out7[0] = c.last_pairs;
+  out7[1] = c.last_items;
   out7[2] = c.stats[0];
   out7[3] = c.stats[1];
   out7[4] = c.stats[2];
@@ -670,7 +689,6 @@ extern "C" int32_t nedf_shade_deferred(const nedf_scene* scene, const nedf_rays*
   k.shade_chord = 0;
   for (int c = 0; c < 3; ++c) k.clear_rgb[c] = opts->clear_rgb[c];
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_reset_status, dim3(1), dim3(64), 0, s, k.status);
   stage_shade(k, s, id, P.nerf, opts->dtype, opts->rs_sigma > 0.0f ? opts->rs_samples : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "nedf_shade_deferred");
@@ -921,7 +939,8 @@ namespace {
 std::mutex g_tune_mu;
 // [kernel][dtype]: 10 * workgroups per CU + chunks per superchunk; for
 // NEDF_TUNE_SLABS the number of depth slabs of the network stage
-int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 14}, {8, 8, 8}};
+// (NEDF_SLABS_DEFAULT: chosen by the size of the call)
+int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 14}, {NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT}};
 
 int tune_candidates(int kernel, int dtype, int32_t* out) {
   if (kernel < 0 || kernel > 2 || dtype < 0 || dtype > 2) return 0;

@@ -57,10 +57,11 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   __shared__ int s_item;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const uint32_t stash = eng::lds_offset(s_stash) + 16u * threadIdx.x;
-  PairList* PL = a.L;  // the current depth slab
+  __shared__ ItemTable s_tab;  // the current depth slab
   PairList* FBL = &a.C->B;
-  const int total = PL->total_items;
-  if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
+  build_items(a, s_tab, 32 * NW);
+  const int total = s_tab.total;
+  if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
   __syncthreads();
   int item = s_item;
   int cur = 0;
@@ -68,15 +69,15 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   int n_hit = 0, n_fb = 0, n_miss = 0;
   while (item < total) {
     __syncthreads();
-    if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
+    if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
     __syncthreads();
     const int next = s_item;
-    const int obj = item_object(PL, a.n_obj, item);
-    const int first = (item - PL->item_start[obj]) * (32 * NW) + wave * 32 + (lane & 31);
+    const int obj = item_object(s_tab, a.n_obj, item);
+    const int first = (item - s_tab.start[obj]) * (32 * NW) + wave * 32 + (lane & 31);
     const ObjDesc& od = a.obj[obj];
     const uint8_t* blob = od.nedf_blob;
     const nedf_cls_header* hc = reinterpret_cast<const nedf_cls_header*>(blob);
-    const uint8_t* next_blob = next < total ? a.obj[item_object(PL, a.n_obj, next)].nedf_blob : nullptr;
+    const uint8_t* next_blob = next < total ? a.obj[item_object(s_tab, a.n_obj, next)].nedf_blob : nullptr;
     const float l = od.bound;
     const uint8_t* head = blob + uniform_load_u64(&hc->off_head);
     const float* hbias = reinterpret_cast<const float*>(blob + uniform_load_u64(&hc->off_head_bias));
@@ -85,8 +86,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
     const uint8_t* tail = blob + uniform_load_u64(&hc->off_tail);
     const int nblk = int(uniform_load_u32(&hc->n_blocks));
     // ---- the pair's line
-    const bool valid = first < PL->cnt[obj];
-    const uint2 pr = a.pairs[PL->off[obj] + (valid ? first : 0)];
+    const bool valid = first < s_tab.cnt[obj];
+    const uint2 pr = a.pairs[s_tab.off[obj] + (valid ? first : 0)];
     f2 q[3], dv[3];
     {
       const W2L g = load_w2l(a.w2l, int(pr.y));
@@ -256,15 +257,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
 }  // namespace
 
 void launch_nedf_cls(const KArgs& k, hipStream_t s, int dtype) {
-  static int ncu = 0;
-  if (ncu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      ncu = 256;
-  }
-  if (dtype == NEDF_BF16) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(ncu), dim3(256), 0, s, k);
-  else hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(ncu), dim3(256), 0, s, k);
+  if (dtype == NEDF_BF16) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+  else hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(cu_count()), dim3(256), 0, s, k);
 }
 
 }  // namespace nedf

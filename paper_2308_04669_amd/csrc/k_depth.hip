@@ -1,7 +1,8 @@
-// Depth stage kernels: culling/binning into per-object pair lists, the plain
-// volume-rendering marcher (Eq. 5) on analytic and MLP fields, the NeDF
-// intersection network (Eq. 1, 2, 7) with routing of uncertain pairs to the
-// marcher, and the packed-key composition (Alg. 1, step 1).
+// Depth stage kernels around the networks: culling/binning into per-object
+// pair lists, the depth-slab filters of the network stage, the depth test of
+// its fallback list, the plain volume-rendering marcher (Eq. 5) on analytic
+// fields, and the packed-key composition (Alg. 1, step 1).
+#include <algorithm>
 #include <cstring>
 
 #include "pipeline.h"
@@ -195,6 +196,33 @@ __global__ __launch_bounds__(256) void k_cull(KArgs a) {
     bd.prune = bd.any && a.clip && cmin > 0.5f && dl > 0.f;
   }
   PairList* L = &a.C->A;
+  __shared__ int s_seg[NEDF_MAX_OBJECTS], s_lim[NEDF_MAX_OBJECTS];
+  if (PASS == 1 && t < 64) {
+    // segment offsets of list A, clamped to the capacity, from the counts of
+    // pass 0 (the first workgroup records them; clamped counts give the same
+    // offsets, so it does not matter which of them another workgroup reads)
+    const int64_t c = t < a.n_obj ? L->cnt[t] : 0;
+    int64_t total;
+    const int64_t off = wave_prefix(c, t, total);
+    const int64_t o0 = min(off, a.capacity), lim = min(off + c, a.capacity) - o0;
+    if (t < NEDF_MAX_OBJECTS) {
+      s_seg[t] = int(o0);
+      s_lim[t] = int(lim);
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+      const int items = t < a.n_obj && ((a.item_mask >> t) & 1u) ? int((lim + a.item_pairs - 1) / a.item_pairs) : 0;
+      int all_items;
+      wave_prefix(items, t, all_items);
+      if (t <= a.n_obj) L->off[t] = a.C->B.off[t] = int(o0);
+      if (t < a.n_obj) L->cnt[t] = int(lim);
+      if (t == 0) {
+        const int kept = int(min(total, a.capacity));
+        a.C->last_pairs = a.C->stats[4] = kept;  // pairs after culling
+        a.C->last_items = all_items;
+        if (total > a.capacity) set_status(a.status, NEDF_ERR_CAPACITY);
+      }
+    }
+  }
   if (t < NEDF_MAX_OBJECTS) s_cnt[t] = 0;
   float dlo = INFINITY, dhi = 0.0f;  // range of the pairs' depth bounds (pass 0)
   __syncthreads();
@@ -264,9 +292,9 @@ __global__ __launch_bounds__(256) void k_cull(KArgs a) {
           off = __shfl(off, leader);
           if (pass) {
             const int pos = s_base[obj] + off + __popcll(m & ((1ull << lane) - 1ull));
-            if (pos < L->cnt[obj]) {
-              a.pairs[L->off[obj] + pos] = make_uint2(uint32_t(ray), uint32_t(k));
-              a.pair_dm[L->off[obj] + pos] = dm;
+            if (pos < s_lim[obj]) {
+              a.pairs[s_seg[obj] + pos] = make_uint2(uint32_t(ray), uint32_t(k));
+              a.pair_dm[s_seg[obj] + pos] = dm;
             }
           }
         }
@@ -308,57 +336,6 @@ __global__ __launch_bounds__(256) void k_cull(KArgs a) {
   }
 }
 
-// Segment offsets of list A (clamped to capacity) and work items over the
-// objects in item_mask.  List B gets the same segments, empty.
-__global__ void k_scan_A(KArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  PairList* L = &a.C->A;
-  PairList* B = &a.C->B;
-  int64_t off = 0;
-  int items = 0;
-  bool over = false;
-  for (int m = 0; m < a.n_obj; ++m) {
-    int64_t c = L->cnt[m];
-    if (off + c > a.capacity) {
-      c = a.capacity - off > 0 ? a.capacity - off : 0;
-      over = true;
-    }
-    L->cnt[m] = int32_t(c);
-    L->off[m] = int32_t(off);
-    B->off[m] = int32_t(off);
-    B->cnt[m] = 0;
-    L->item_start[m] = items;
-    if ((a.item_mask >> m) & 1u) items += int32_t((c + a.item_pairs - 1) / a.item_pairs);
-    L->fill[m] = 0;
-    off += c;
-  }
-  L->off[a.n_obj] = int32_t(off);
-  B->off[a.n_obj] = int32_t(off);
-  L->item_start[a.n_obj] = items;
-  L->total_items = items;
-  L->total_pairs = int32_t(off);
-  L->work_counter = 0;
-  a.C->stats[4] = int32_t(off);  // pairs after culling (kept when later stages rebin list A)
-  if (over) set_status(a.status, NEDF_ERR_CAPACITY);
-}
-
-// Work items over an already-filled list (segments fixed): list B after the
-// network stage, or list A for a second pass with another item size.
-__global__ void k_scan_items(KArgs a, PairList* L) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int items = 0, total = 0;
-  for (int m = 0; m < a.n_obj; ++m) {
-    L->item_start[m] = items;
-    const int c = L->cnt[m];
-    if ((a.item_mask >> m) & 1u) items += (c + a.item_pairs - 1) / a.item_pairs;
-    total += c;
-  }
-  L->item_start[a.n_obj] = items;
-  L->total_items = items;
-  L->total_pairs = total;
-  L->work_counter = 0;
-}
-
 // Front-to-back network stage.  A pair can report no depth below its bound
 // s (t_perp - l) (kept per pair by the culling pass, with the bounds' range):
 // the network's depth is s (t_perp - l clamp(mu_hat, -1, 1)) and the
@@ -368,23 +345,13 @@ __global__ void k_scan_items(KArgs a, PairList* L) {
 // cannot win the min-reduce and is skipped.  The result is the same as
 // evaluating every pair, whatever the slab boundaries.
 
-__global__ void k_slab_begin(KArgs a) {
-  if (blockIdx.x != 0) return;
-  PairList* S = &a.C->S;
-  const PairList* A = &a.C->A;
-  for (int m = threadIdx.x; m < NEDF_MAX_OBJECTS; m += blockDim.x) {
-    S->cnt[m] = 0;
-    S->off[m] = A->off[m];
-  }
-}
-
 // Candidates a lane tests at once in the slab filters.
 constexpr int SLAB_U = 8;
 
 // Wave-aggregated append of the kept pairs (SLAB_U per lane) to their
 // objects' segments of list S: one atomic per object present reserves the
 // slots of all of them.  Called with the whole wave active.
-__device__ __forceinline__ void push_slab(const KArgs& a, PairList* S, int lane, const bool (&keep)[SLAB_U],
+__device__ __forceinline__ void push_slab(const KArgs& a, int32_t* cnt, int lane, const bool (&keep)[SLAB_U],
                                           const int (&m)[SLAB_U], const uint2 (&pr)[SLAB_U]) {
   uint64_t pend[SLAB_U];
 #pragma unroll
@@ -407,8 +374,8 @@ __device__ __forceinline__ void push_slab(const KArgs& a, PairList* S, int lane,
       pend[u] &= ~mk;
     }
     int base = 0;
-    if (lane == 0) base = atomicAdd(&S->cnt[m0], tot);
-    const int run = S->off[m0] + __builtin_amdgcn_readfirstlane(base);
+    if (lane == 0) base = atomicAdd(&cnt[m0], tot);
+    const int run = a.C->A.off[m0] + __builtin_amdgcn_readfirstlane(base);
     for (int u = 0; u < SLAB_U; ++u)
       if (mine[u]) a.pairsS[run + pos[u]] = pr[u];
   }
@@ -420,7 +387,7 @@ __device__ __forceinline__ void push_slab(const KArgs& a, PairList* S, int lane,
 // then takes them 64 * SLAB_U at a time, SLAB_U per lane, so that the bound,
 // pair and key reads of all of them are in flight together.  Called with the
 // whole wave active.
-__device__ __forceinline__ void slab_candidates(const KArgs& a, PairList* S, int* cand, int lane, int q0,
+__device__ __forceinline__ void slab_candidates(const KArgs& a, int32_t* cnt, int* cand, int lane, int q0,
                                                 uint32_t hits) {
   const int c = __popc(hits);
   int incl = c;
@@ -461,7 +428,7 @@ __device__ __forceinline__ void slab_candidates(const KArgs& a, PairList* S, int
       // margin against last-bit differences between kernels
       keep[u] = keep[u] && !(depth_limit(a, pr[u].x) < dm[u] - (1e-5f * dm[u] + 1e-5f));
     }
-    push_slab(a, S, lane, keep, m, pr);
+    push_slab(a, cnt, lane, keep, m, pr);
   }
   __builtin_amdgcn_wave_barrier();
 }
@@ -476,7 +443,7 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
   __shared__ int s_cand[4][SLAB_BLOCK];
   __shared__ int s_off[NEDF_MAX_OBJECTS + 1];
   const PairList* A = &a.C->A;
-  PairList* S = &a.C->S;
+  int32_t* cnt = a.C->slab_cnt[0];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // segment offsets and the slab map, read once (the loop below stores to
   // global memory, so the compiler could not keep them in registers)
@@ -530,7 +497,7 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bits |= __shfl_xor(bits, off);
     if (lane == 0) a.slab_mask[blk] = bits;
-    slab_candidates(a, S, s_cand[wave], lane, q0, hits);
+    slab_candidates(a, cnt, s_cand[wave], lane, q0, hits);
   }
 }
 
@@ -540,8 +507,14 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
 __global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
   __shared__ int s_cand[4][SLAB_BLOCK];
   const PairList* A = &a.C->A;
-  PairList* S = &a.C->S;
+  int32_t* cnt = a.C->slab_cnt[slab & 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the other set, free since the slab before has been evaluated, becomes
+  // the next slab's
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < NEDF_MAX_OBJECTS) a.C->slab_cnt[(slab + 1) & 1][threadIdx.x] = 0;
+    if (threadIdx.x == 0) a.C->slab_work[(slab + 1) & 1] = 0;
+  }
   const int total = A->off[a.n_obj];
   const int nblk = (total + SLAB_BLOCK - 1) / SLAB_BLOCK;
   const uint4* sv = reinterpret_cast<const uint4*>(a.pair_slab);
@@ -563,7 +536,7 @@ __global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
       const int rem = total - q0;
       if (rem < 16) hits &= (1u << rem) - 1u;
     }
-    slab_candidates(a, S, s_cand[wave], lane, q0, hits);
+    slab_candidates(a, cnt, s_cand[wave], lane, q0, hits);
   }
 }
 
@@ -572,11 +545,7 @@ __global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
 // win the min-reduce, since every marcher sample lies inside the chord and
 // the marched depth is a weighted mean of sample depths.  Kept pairs are
 // compacted into list A's pair array (free after the network stage) at list
-// B's segment offsets; list B's counts are replaced by the kept counts.
-__global__ void k_zero_fill(KArgs a) {
-  if (blockIdx.x == 0 && threadIdx.x < NEDF_MAX_OBJECTS) a.C->B.fill[threadIdx.x] = 0;
-}
-
+// B's segment offsets, and counted in its fill counters.
 __global__ void k_fallback_depth_test(KArgs a, uint2* out) {
   PairList* B = &a.C->B;
   const int lane = threadIdx.x & 63;
@@ -611,25 +580,13 @@ __global__ void k_fallback_depth_test(KArgs a, uint2* out) {
   }
 }
 
-__global__ void k_fallback_commit(KArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  PairList* B = &a.C->B;
-  int kept = 0;
-  for (int m = 0; m < a.n_obj; ++m) {
-    B->cnt[m] = B->fill[m];
-    kept += B->fill[m];
-  }
-  a.C->stats[3] = kept;
-}
-
 // One thread per pair of an analytic object in `mask`; sequential
 // compensated scan.
 __global__ void k_march_analytic(KArgs a, uint32_t mask) {
-  const PairList* L = a.L;
   for (int m = 0; m < a.n_obj; ++m) {
     const ObjDesc od = a.obj[m];
     if (od.field == NEDF_FIELD_MLP || !((mask >> m) & 1u)) continue;
-    const int cnt = L->cnt[m], off = L->off[m];
+    const int cnt = a.lcnt[m], off = a.loff[m];
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < cnt; q += gridDim.x * blockDim.x) {
       const uint2 pr = a.pairs[off + q];
       const W2L g = load_w2l(a.w2l, int(pr.y));
@@ -663,243 +620,43 @@ __global__ void k_march_analytic(KArgs a, uint32_t mask) {
   }
 }
 
-// Matrix-core marcher: a workgroup takes items of 4 pairs (one per wave) of
-// one object from list a.L; each wave marches its pair in chunks of 32 NB
-// samples through the register-resident density network (NB blocks of 32
-// share every weight read from LDS), then scans each block's optical depths
-// across the wave in sample order, so that the sums are the same for any NB.
-template <int DT, int WIDTH, int NHID, int L, int SBX, int OCC, int NB, int NW>
-__global__ __launch_bounds__(64 * NW, OCC) void k_march_mlp(KArgs a) {
-  using T = eng::Tr<DT>;
-  constexpr int KS0 = eng::ks_for_slots<DT>(3 * L + 2);
-  constexpr int KSH = WIDTH / T::KPS;
-  constexpr int CHUNK = eng::cmax(eng::chunk_bytes<DT>(KS0, 0), eng::chunk_bytes<DT>(KSH, 1));
-  constexpr int SPC = 32 * NB;  // samples per wave per chunk
-  __shared__ __attribute__((aligned(16))) uint8_t lds[eng::NBUF * eng::slot_bytes(CHUNK, SBX)];
-  __shared__ int s_item;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  PairList* PL = a.L;
-  const int N = a.n_samples;
-  const int n_chunks = (N + SPC - 1) / SPC;
-  const int total = PL->total_items;
-  // one item of lookahead: the next item is claimed during the current
-  // item's last pass so that its weights stream in behind this one's
-  if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
-  __syncthreads();
-  int item = s_item;
-  int slot = 0;
-  bool primed = false;
-  while (item < total) {
-    const int obj = item_object(PL, a.n_obj, item);
-    const int local = (item - PL->item_start[obj]) * NW + wave;
-    const bool valid = local < PL->cnt[obj];
-    const uint2 pr = a.pairs[PL->off[obj] + (valid ? local : 0)];
-    const ObjDesc& od = a.obj[obj];
-    const uint8_t* blob = od.blob;
-    const nedf_blob_header* hb = reinterpret_cast<const nedf_blob_header*>(blob);
-    const float head_b = uniform_load_f32(blob + uniform_load_u64(&hb->off_head_b));
-    const W2L g = load_w2l(a.w2l, int(pr.y));
-    float o[3], d[3], ol[3], dl[3];
-    make_ray(a.rays, pr.x, o, d);
-    to_local(g, o, d, ol, dl);
-    float ta = 0.f, tb = 0.f;
-    bool seg = true;
-    if (a.clip) {
-      seg = sphere_chord(ol, dl, od.bound, ta, tb);
-      if (!seg) { ta = 0.f; tb = 0.f; }
-    } else {
-      ta = a.t_near * g.inv_s;
-      tb = a.t_far * g.inv_s;
-    }
-    const float delta = (tb - ta) / float(N);
-    const float pa[3] = {fmaf(ta, dl[0], ol[0]), fmaf(ta, dl[1], ol[1]), fmaf(ta, dl[2], ol[2])};
-    float carry = 0.f, carry_c = 0.f, sw = 0.f, sw_c = 0.f, swt = 0.f, swt_c = 0.f;
-    int next = total;
-    for (int c = 0; c < n_chunks; ++c) {
-      const bool last = c + 1 == n_chunks;
-      if (last) {
-        __syncthreads();  // every wave has read s_item
-        if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
-        __syncthreads();
-        next = s_item;
-      }
-      const uint8_t* next_blob = !last ? blob : (next < total ? a.obj[item_object(PL, a.n_obj, next)].blob : nullptr);
-      typename T::frag Benc[NB][KS0];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float tr = (float(c * SPC + 32 * nb + (lane & 31)) + 0.5f) * delta;
-        float p[3] = {fmaf(tr, dl[0], pa[0]), fmaf(tr, dl[1], pa[1]), fmaf(tr, dl[2], pa[2])};
-        eng::encode_input<DT, 3, L, KS0>(p, half, Benc[nb]);
-      }
-      float partial[NB][1];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) partial[nb][0] = 0.f;
-      typename T::frag Blast[NB][KSH];
-      eng::trunk<DT, WIDTH, KS0, NHID, 1, CHUNK, false, 0, WIDTH / 32, SBX, NB, NW>(hb, blob, Benc, lds, partial,
-                                                                               Blast, nullptr, &slot, next_blob,
-                                                                               primed);
-      primed = next_blob != nullptr;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int si = c * SPC + 32 * nb + (lane & 31);
-        const float tr = (float(si) + 0.5f) * delta;
-        const float p[3] = {fmaf(tr, dl[0], pa[0]), fmaf(tr, dl[1], pa[1]), fmaf(tr, dl[2], pa[2])};
-        const float u = partial[nb][0] + __shfl_xor(partial[nb][0], 32) + head_b;
-        float v = mlp_sigma(od, u, p[0], p[1], p[2]) * delta;
-        if (lane >= 32 || si >= N || !seg) v = 0.f;
-        // inclusive scan of optical depth over the wave (sample order = lane order)
-        float incl = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const float y = __shfl_up(incl, off);
-          if (lane >= off) incl += y;
-        }
-        const float tau = (carry + carry_c) + (incl - v);
-        const float w = expf(-tau) * one_minus_exp_neg(v);
-        float ws = w, wts = w * (ta + tr);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-          ws += __shfl_xor(ws, off);
-          wts += __shfl_xor(wts, off);
-        }
-        // a block wholly past the last sample adds exact zeros
-        neu_add(sw, sw_c, ws);
-        neu_add(swt, swt_c, wts);
-        neu_add(carry, carry_c, __shfl(incl, 63));
-      }
-    }
-    if (lane == 0 && valid && seg) {
-      const float A = sw + sw_c;
-      if (A >= a.hit_thr && A > 0.0f) emit_key(a, pr.x, pr.y, g.s * ((swt + swt_c) / A));
-      atomicMax(&a.opac[pr.x], __float_as_uint(fmaxf(A, 0.0f)));
-    }
-    item = next;
+// Keys -> depth, id and opacity.  A workgroup takes a contiguous range of
+// rays; with BIN it also counts its hit pixels per object of `mask` for the
+// binning that follows (one global atomic per workgroup and object).  The
+// first workgroup totals the marched fallback pairs.
+template <bool BIN>
+__global__ __launch_bounds__(256) void k_finalize(KArgs a, uint32_t mask) {
+  __shared__ int s_cnt[NEDF_MAX_OBJECTS];
+  const int t = threadIdx.x, lane = t & 63;
+  if (BIN && t < NEDF_MAX_OBJECTS) s_cnt[t] = 0;
+  if (BIN) __syncthreads();
+  if (blockIdx.x == 0 && t < 64) {
+    int kept;
+    wave_prefix(t < a.n_obj ? a.C->B.fill[t] : 0, t, kept);
+    if (t == 0) a.C->stats[3] = kept;
   }
-}
-
-// NeDF stage: a workgroup takes items of 128 NB pairs (32 NB per wave) of
-// one object; each lane pair evaluates the intersection network on its pairs'
-// line coordinates (NB blocks of 32 pairs share every weight read from LDS).
-// Confident hits go to the key buffer, uncertain pairs (and origins inside
-// the bounding sphere) to list B for the marcher.
-template <int DT, int WIDTH, int NHID, int L, int SBX, int OCC, int NB, int NW>
-__global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
-  using T = eng::Tr<DT>;
-  constexpr int PPW = 32 * NB;  // pairs per wave and item
-  constexpr int KS0 = eng::ks_for_slots<DT>(6 * L + 3);
-  constexpr int KSH = WIDTH / T::KPS;
-  constexpr int CHUNK = eng::cmax(eng::chunk_bytes<DT>(KS0, 0), eng::chunk_bytes<DT>(KSH, 2));
-  __shared__ __attribute__((aligned(16))) uint8_t lds[eng::NBUF * eng::slot_bytes(CHUNK, SBX)];
-  // per-lane pair state parked across the network (keeps registers free)
-  constexpr int NT = 64 * NW;
-  __shared__ __attribute__((aligned(16))) uint8_t s_stash[16 * NB * NT];
-  __shared__ int s_item;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  const uint32_t stash = eng::lds_offset(s_stash) + 16u * threadIdx.x;
-  PairList* PL = a.L;  // the current depth slab
-  PairList* FB = &a.C->B;
-  const int total = PL->total_items;
-  if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
-  __syncthreads();
-  int item = s_item;
-  int slot = 0;
-  bool primed = false;
-  // routing counts, per wave, flushed once at the end
-  int n_hit = 0, n_fb = 0, n_miss = 0;
-  while (item < total) {
-    // claim the next item now so that its weights stream in behind this pass
+  const int64_t per = bin_span(a.n_rays, gridDim.x);
+  const int64_t p0 = int64_t(blockIdx.x) * per;
+  const int64_t p1 = min(p0 + per, a.n_rays);
+  for (int64_t pb = p0; pb < p1; pb += 256) {
+    const int64_t i = pb + t;
+    int inst = -1;
+    if (i < p1) {
+      const uint64_t k = a.keys[i];
+      const bool hit = k != NEDF_KEY_EMPTY;
+      if (hit) inst = int32_t(uint32_t(k & 0xffffffffu));
+      a.depth[i] = hit ? __uint_as_float(uint32_t(k >> 32)) : __int_as_float(0x7f800000);
+      if (a.id) a.id[i] = inst;
+      if (a.opacity) a.opacity[i] = __uint_as_float(a.opac[i]);
+    }
+    if constexpr (BIN) bin_groups(a, inst, mask, lane, [&](int o, uint64_t match, bool) {
+      if (lane == __ffsll((unsigned long long)match) - 1) atomicAdd(&s_cnt[o], __popcll(match));
+    });
+  }
+  if constexpr (BIN) {
     __syncthreads();
-    if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
-    __syncthreads();
-    const int next = s_item;
-    const int obj = item_object(PL, a.n_obj, item);
-    const int first = (item - PL->item_start[obj]) * (PPW * NW) + wave * PPW + (lane & 31);
-    const ObjDesc& od = a.obj[obj];
-    const uint8_t* blob = od.nedf_blob;
-    const uint8_t* next_blob = next < total ? a.obj[item_object(PL, a.n_obj, next)].nedf_blob : nullptr;
-    const nedf_blob_header* hb = reinterpret_cast<const nedf_blob_header*>(blob);
-    const float* hbias_p = reinterpret_cast<const float*>(blob + uniform_load_u64(&hb->off_head_b));
-    const float hbias[2] = {uniform_load_f32(hbias_p), uniform_load_f32(hbias_p + 1)};
-    const float l = od.bound;
-    typename T::frag Benc[NB][KS0];
-    const float in_scale = DT == 2 ? uniform_load_f32(blob + uniform_load_u64(&hb->off_scales)) : 1.0f;
-    // lane-half-dependent encoding constants are recomputed per pass rather
-    // than hoisted out of the loop (where they would stay live, and spill,
-    // across the network)
-    int half_v = half;
-    asm volatile("" : "+v"(half_v));
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int local = first + 32 * nb;
-      const bool valid = local < PL->cnt[obj];
-      const uint2 pr = a.pairs[PL->off[obj] + (valid ? local : 0)];
-      const W2L g = load_w2l(a.w2l, int(pr.y));
-      float o[3], d[3], dlo[3], ol[3], pl[6], pllo[6], tperp;
-      make_ray(a.rays, pr.x, o, d, dlo);
-      local_line(g, o, d, dlo, pl, pllo, tperp, ol);
-      const bool inside = ol[0] * ol[0] + ol[1] * ol[1] + ol[2] * ol[2] < l * l;
-      eng::encode_input<DT, 6, L, KS0>(pl, pllo, half_v, Benc[nb], in_scale);
-      // ray and instance ids (< 2^31, flags in bit 31), t_perp and s
-      eng::lds_write16(stash + uint32_t(nb) * (16u * NT),
-                       eng::u32x4{pr.x | (valid ? 0x80000000u : 0u), pr.y | (inside ? 0x80000000u : 0u),
-                                  __float_as_uint(tperp), __float_as_uint(g.s)});
-    }
-    float partial[NB][2];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) partial[nb][0] = partial[nb][1] = 0.f;
-    typename T::frag Blast[NB][KSH];
-    eng::trunk<DT, WIDTH, KS0, NHID, 2, CHUNK, false, 0, WIDTH / 32, SBX, NB, NW>(hb, blob, Benc, lds, partial, Blast,
-                                                                             nullptr, &slot, next_blob, primed);
-    primed = next_blob != nullptr;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      eng::u32x4 st = eng::lds_read16<0>(stash + uint32_t(nb) * (16u * NT)), d1 = st, d2 = st, d3 = st;
-      eng::lds_wait4<0>(st, d1, d2, d3);
-      const uint2 prs = make_uint2(st.x & 0x7FFFFFFFu, st.y & 0x7FFFFFFFu);
-      const bool valid_s = (st.x >> 31) != 0, inside_s = (st.y >> 31) != 0;
-      const float mu_hat = partial[nb][0] + __shfl_xor(partial[nb][0], 32) + hbias[0];
-      const float z = partial[nb][1] + __shfl_xor(partial[nb][1], 32) + hbias[1];
-      const float p = sigmoidf_(z);
-      const float D = __uint_as_float(st.w) * (__uint_as_float(st.z) - l * fminf(fmaxf(mu_hat, -1.0f), 1.0f));
-      const bool mine = valid_s && half == 0;
-      const bool to_fb = mine && (inside_s || (p >= a.p_lo && p <= a.p_hi));
-      const bool hit = mine && !to_fb && p > a.p_hi && D > 0.0f;
-      if (hit) emit_key(a, prs.x, prs.y, D);
-      // wave-aggregated push into the object's segment of list B
-      const uint64_t m = __ballot(to_fb);
-      if (m) {
-        const int leader = __ffsll((unsigned long long)m) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&FB->cnt[obj], __popcll(m));
-        base = __shfl(base, leader);
-        if (to_fb) a.pairsB[FB->off[obj] + base + __popcll(m & ((1ull << lane) - 1ull))] = prs;
-      }
-      const uint64_t mh = __ballot(hit), mv = __ballot(mine);
-      n_hit += __popcll(mh);
-      n_fb += __popcll(m);
-      n_miss += __popcll(mv) - __popcll(mh) - __popcll(m);
-    }
-    item = next;
+    if (t < a.n_obj && s_cnt[t]) atomicAdd(&a.C->R.cnt[t], s_cnt[t]);
   }
-  if (lane == 0 && (n_hit | n_fb | n_miss)) {
-    atomicAdd(&a.C->stats[0], n_hit);
-    atomicAdd(&a.C->stats[1], n_fb);
-    atomicAdd(&a.C->stats[2], n_miss);
-  }
-}
-
-__global__ void k_finalize(KArgs a) {
-  const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= a.n_rays) return;
-  const uint64_t k = a.keys[i];
-  if (k == NEDF_KEY_EMPTY) {
-    a.depth[i] = __int_as_float(0x7f800000);
-    if (a.id) a.id[i] = -1;
-  } else {
-    a.depth[i] = __uint_as_float(uint32_t(k >> 32));
-    if (a.id) a.id[i] = int32_t(uint32_t(k & 0xffffffffu));
-  }
-  if (a.opacity) a.opacity[i] = __uint_as_float(a.opac[i]);
 }
 
 // Buffer reuse (Sec. "CUDA implementation"): the depth keys of several
@@ -932,76 +689,9 @@ __global__ void k_merge_keys(KArgs a, KeySets ks) {
     reinterpret_cast<int32_t*>(a.C)[w] = w == int64_t(offsetof(WsCounters, dmin_bits) / 4) ? 0x7F800000 : 0;
 }
 
-int cu_count() {
-  static int ncu = 0;
-  if (ncu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      ncu = 256;
-  }
-  return ncu;
-}
-
-// Launch shape of the 256-wide BF16/FP8 kernels from the tuning table: value
-// 100 * (32-row blocks per wave - 1) + 10 * occupancy + superchunk (blocks
-// sharing each weight read, workgroups per CU, chunks per copy); other shapes
-// use one block, one workgroup per CU and the default superchunk.  The grid
-// is persistent: one workgroup per CU and occupancy level.
-// Tuning value of the matrix-core kernels: 1000 * (workgroup waves / 4 - 1) +
-// 100 * (row blocks per wave - 1) + 10 * workgroups per CU + chunks per
-// superchunk.
-int tune_waves(int v) { return v >= 1000 ? 8 : 4; }
-int nedf_rows(int v) { return v % 1000 >= 100 ? 2 : 1; }
-
-template <int DT, int WIDTH, int NHID, int L>
-void launch_march_mlp(const KArgs& k, hipStream_t s) {
-  const dim3 b4(256), b8(512), g1(cu_count()), g2(2 * cu_count());
-  if constexpr (DT == 1 && WIDTH == 256) {
-    switch (tune_value(NEDF_TUNE_MARCH, DT)) {
-      case 11: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 1, 1, 1, 4>), g1, b4, 0, s, k); return;
-      case 21: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 1, 2, 1, 4>), g2, b4, 0, s, k); return;
-      case 111: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 1, 1, 2, 4>), g1, b4, 0, s, k); return;
-      case 112: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 2, 1, 2, 4>), g1, b4, 0, s, k); return;
-      case 1011: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 1, 1, 1, 8>), g1, b8, 0, s, k); return;
-      case 1012: hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, 2, 1, 1, 8>), g1, b8, 0, s, k); return;
-      default: break;
-    }
-  }
-  hipLaunchKernelGGL((k_march_mlp<DT, WIDTH, NHID, L, eng::sb_default<DT>(), 1, 1, 4>), g1, b4, 0, s, k);
-}
-
-template <int DT>
-void launch_nedf_net(const KArgs& k, hipStream_t s, int v) {
-  const dim3 b4(256), b8(512), g1(cu_count()), g2(2 * cu_count());
-  if constexpr (DT == 2) {
-    switch (v) {
-      case 11: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 4>), g1, b4, 0, s, k); return;
-      case 12: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 1, 1, 4>), g1, b4, 0, s, k); return;
-      case 21: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 2, 1, 4>), g2, b4, 0, s, k); return;
-      case 22: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 2, 1, 4>), g2, b4, 0, s, k); return;
-      case 1011: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 8>), g1, b8, 0, s, k); return;
-      case 1012: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 1, 1, 8>), g1, b8, 0, s, k); return;
-      case 1014: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 8>), g1, b8, 0, s, k); return;
-      default: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 4>), g1, b4, 0, s, k); return;
-    }
-  } else if constexpr (DT == 1) {
-    switch (v) {
-      case 11: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 4>), g1, b4, 0, s, k); return;
-      case 21: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 2, 1, 4>), g2, b4, 0, s, k); return;
-      case 111: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 2, 4>), g1, b4, 0, s, k); return;
-      case 112: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 1, 2, 4>), g1, b4, 0, s, k); return;
-      case 1011: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 8>), g1, b8, 0, s, k); return;
-      case 1012: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 1, 1, 8>), g1, b8, 0, s, k); return;
-      default: hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 2, 1, 1, 4>), g1, b4, 0, s, k); return;
-    }
-  } else if constexpr (DT == 3) {
-    // MX: superchunks of four blocks; eight waves (items of 256 pairs) or four
-    if (v >= 1000) hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 8>), g1, b8, 0, s, k);
-    else hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 4>), g1, b4, 0, s, k);
-  } else {
-    hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 4>), g1, b4, 0, s, k);
-  }
+// Most pairs that list A of this call can hold.
+int64_t pair_bound(const KArgs& k) {
+  return std::max<int64_t>(1, std::min<int64_t>(k.capacity, k.n_rays * k.n_inst));
 }
 
 unsigned grid_for(int64_t n) {
@@ -1011,9 +701,15 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
-int march_waves(int dtype, int width) {
-  if (dtype != NEDF_BF16 || width != 256) return 4;
-  return tune_waves(tune_value(NEDF_TUNE_MARCH, dtype));
+int cu_count() {
+  static int ncu = 0;
+  if (ncu == 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      ncu = 256;
+  }
+  return ncu;
 }
 
 bool march_mlp_supported(int dtype, int width, int n_hidden, int L) {
@@ -1046,14 +742,12 @@ void stage_init_cull(const KArgs& k0, hipStream_t s, uint32_t item_mask, int ite
   KArgs k = k0;
   k.item_mask = item_mask;
   k.item_pairs = item_pairs;
-  k.L = &k.C->A;
   const unsigned g = grid_for(k.n_rays);
   prof_mark("depth.cull", s, true);
   hipLaunchKernelGGL(k_init, dim3(g), dim3(256), 0, s, k);
   if (k.rays.kind == 0) {
     const dim3 tg((k.rays.width + CULL_TILE - 1) / CULL_TILE, (k.rays.height + CULL_TILE - 1) / CULL_TILE);
     hipLaunchKernelGGL((k_cull<0, true>), tg, dim3(256), 0, s, k);
-    hipLaunchKernelGGL(k_scan_A, dim3(1), dim3(64), 0, s, k);
     hipLaunchKernelGGL((k_cull<1, true>), tg, dim3(256), 0, s, k);
   } else {
     dim3 ag(g);
@@ -1062,7 +756,6 @@ void stage_init_cull(const KArgs& k0, hipStream_t s, uint32_t item_mask, int ite
       ag = dim3((k.ray_grid_w + CULL_TILE - 1) / CULL_TILE, unsigned((h + CULL_TILE - 1) / CULL_TILE));
     }
     hipLaunchKernelGGL((k_cull<0, false>), ag, dim3(256), 0, s, k);
-    hipLaunchKernelGGL(k_scan_A, dim3(1), dim3(64), 0, s, k);
     hipLaunchKernelGGL((k_cull<1, false>), ag, dim3(256), 0, s, k);
   }
   prof_mark("depth.cull", s, false);
@@ -1073,22 +766,22 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   (void)H;
   (void)Lenc;
   KArgs k = k0;
-  k.L = list_b ? &k.C->B : &k.C->A;
+  PairList* L = list_b ? &k.C->B : &k.C->A;
+  k.lcnt = L->cnt;
+  k.loff = L->off;
+  k.lwork = &L->work_counter;
+  k.item_mask = 0;
+  for (int m = 0; m < k.n_obj; ++m)
+    if (k.obj[m].field == NEDF_FIELD_MLP) k.item_mask |= 1u << m;
   if (list_b) {
     // depth-test the fallback pairs against the network's hits, compacting
     // them into list A's array, which the marcher then reads
     k.pairs = k.pairsB;
-    hipLaunchKernelGGL(k_zero_fill, dim3(1), dim3(64), 0, s, k);
-    hipLaunchKernelGGL(k_fallback_depth_test, dim3(2048), dim3(256), 0, s, k, k0.pairs);
-    hipLaunchKernelGGL(k_fallback_commit, dim3(1), dim3(64), 0, s, k);
+    const int64_t most = pair_bound(k);
+    hipLaunchKernelGGL(k_fallback_depth_test, dim3(unsigned(std::min<int64_t>(2048, grid_for(most)))), dim3(256), 0,
+                       s, k, k0.pairs);
     k.pairs = k0.pairs;
-  }
-  if (list_b) {
-    k.item_mask = 0;
-    for (int m = 0; m < k.n_obj; ++m)
-      if (k.obj[m].field == NEDF_FIELD_MLP) k.item_mask |= 1u << m;
-    k.item_pairs = march_waves(dtype, W);
-    hipLaunchKernelGGL(k_scan_items, dim3(1), dim3(64), 0, s, k, k.L);
+    k.lcnt = L->fill;
   }
   if (analytic_mask) {
     prof_mark(list_b ? "fallback.analytic" : "march.analytic", s, true);
@@ -1097,13 +790,7 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   }
   if (W > 0) {
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, true);
-    if (dtype == NEDF_BF16) {
-      if (W == 256) launch_march_mlp<1, 256, 8, 10>(k, s);
-      else launch_march_mlp<1, 64, 3, 6>(k, s);
-    } else {
-      if (W == 256) launch_march_mlp<0, 256, 8, 10>(k, s);
-      else launch_march_mlp<0, 64, 3, 6>(k, s);
-    }
+    launch_march(k, s, dtype, W);
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, false);
   }
 }
@@ -1111,23 +798,31 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
 void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, int n_slabs, bool classifier) {
   KArgs k = k0;
   prof_mark("infer.nedf", s, true);
-  k.L = &k.C->S;
-  k.pairs = k.pairsS;
   k.item_mask = nedf_mask;
+  k.loff = k.C->A.off;
   // launch shape from the tuning table, fixed for all slabs of the stage
   const int v = dtype == NEDF_F32 ? 11 : dtype == NEDF_FP8_MX ? 1014 : tune_value(NEDF_TUNE_NEDF, dtype);
-  k.item_pairs = classifier ? 32 * 4 : 32 * tune_waves(v) * nedf_rows(v);
+  const dim3 fg(unsigned(std::min<int64_t>(2048, (pair_bound(k) + 4 * SLAB_BLOCK - 1) / (4 * SLAB_BLOCK))));
+  // one slab: nothing can be skipped before the network has run (other than
+  // behind analytic objects and light distances, which pays for a filter in
+  // large calls), so it takes list A as it is
+  bool others = k.ray_tmax != nullptr;
+  for (int m = 0; m < k.n_obj; ++m) others |= !((nedf_mask >> m) & 1u);
+  const bool direct = n_slabs == 1 && !(others && pair_bound(k) > (1 << 20));
   for (int slab = 0; slab < n_slabs; ++slab) {
-    hipLaunchKernelGGL(k_slab_begin, dim3(1), dim3(64), 0, s, k);
-    if (slab == 0) hipLaunchKernelGGL(k_slab_first, dim3(2048), dim3(256), 0, s, k0, nedf_mask, n_slabs);
-    else hipLaunchKernelGGL(k_slab_next, dim3(2048), dim3(256), 0, s, k0, slab);
-    hipLaunchKernelGGL(k_scan_items, dim3(1), dim3(64), 0, s, k, k.L);
+    if (direct) {
+      k.lcnt = k.C->A.cnt;
+      k.lwork = &k.C->slab_work[0];
+    } else {
+      k.pairs = k.pairsS;
+      k.lcnt = k.C->slab_cnt[slab & 1];
+      k.lwork = &k.C->slab_work[slab & 1];
+      if (slab == 0) hipLaunchKernelGGL(k_slab_first, fg, dim3(256), 0, s, k0, nedf_mask, n_slabs);
+      else hipLaunchKernelGGL(k_slab_next, fg, dim3(256), 0, s, k0, slab);
+    }
     prof_mark("net", s, true);
     if (classifier) launch_nedf_cls(k, s, dtype);
-    else if (dtype == NEDF_FP8) launch_nedf_net<2>(k, s, v);
-    else if (dtype == NEDF_FP8_MX) launch_nedf_net<3>(k, s, v);
-    else if (dtype == NEDF_BF16) launch_nedf_net<1>(k, s, v);
-    else launch_nedf_net<0>(k, s, v);
+    else launch_nedf(k, s, dtype, v);
     prof_mark("net", s, false);
   }
   prof_mark("infer.nedf", s, false);
@@ -1139,9 +834,11 @@ void stage_merge_keys(const KArgs& k, hipStream_t s, const KeySets& ks) {
   prof_mark("compose.merge", s, false);
 }
 
-void stage_finalize(const KArgs& k, hipStream_t s) {
+void stage_finalize(const KArgs& k, hipStream_t s, uint32_t bin_mask) {
   prof_mark("depth.finalize", s, true);
-  hipLaunchKernelGGL(k_finalize, dim3(grid_for(k.n_rays)), dim3(256), 0, s, k);
+  const dim3 g(bin_blocks(k.n_rays));
+  if (bin_mask) hipLaunchKernelGGL(k_finalize<true>, g, dim3(256), 0, s, k, bin_mask);
+  else hipLaunchKernelGGL(k_finalize<false>, g, dim3(256), 0, s, k, bin_mask);
   prof_mark("depth.finalize", s, false);
 }
 

@@ -9,88 +9,79 @@
 namespace nedf {
 namespace {
 
-// Segment offsets and work items of list A over the objects in item_mask.
-__global__ void k_scan_pixels(KArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  PairList* L = &a.C->A;
-  int64_t off = 0;
-  int items = 0;
-  for (int m = 0; m < a.n_obj; ++m) {
-    if (off + L->cnt[m] > a.capacity) {
-      L->cnt[m] = int32_t(a.capacity - off > 0 ? a.capacity - off : 0);
-      set_status(a.status, NEDF_ERR_CAPACITY);
-    }
-    L->off[m] = int32_t(off);
-    L->item_start[m] = items;
-    if ((a.item_mask >> m) & 1u) items += (L->cnt[m] + a.item_pairs - 1) / a.item_pairs;
-    L->fill[m] = 0;
-    off += L->cnt[m];
+// Start of the shading call: the status word, list R and (for the outliers)
+// list B.
+__global__ void k_begin_pixels(KArgs a, int resample) {
+  const int t = threadIdx.x;
+  constexpr int words = int(sizeof(PairList) / 4);
+  if (t == 0) *a.status = 0;
+  for (int i = t; i < words; i += blockDim.x) {
+    reinterpret_cast<int32_t*>(&a.C->R)[i] = 0;
+    if (resample) reinterpret_cast<int32_t*>(&a.C->B)[i] = 0;
   }
-  L->off[a.n_obj] = off;
-  L->item_start[a.n_obj] = items;
-  L->total_items = items;
-  L->total_pairs = off;
-  L->work_counter = 0;
+  if (t == 0 && resample) a.C->stats[1] = 0;
 }
 
-__global__ void k_zero_list(PairList* L) {
-  const int i = threadIdx.x;
-  if (i < int(sizeof(PairList) / 4)) reinterpret_cast<int32_t*>(L)[i] = 0;
-}
-
-// Bin pixels with a valid ID whose object is in `mask` into list A as
-// (pixel, instance) pairs; pass 0 counts, pass 1 writes.  A workgroup takes a
-// contiguous range of pixels and aggregates its counts per object in LDS
-// (lanes of a wave grouped by object, one LDS atomic per group), so global
-// atomics are one per (workgroup, object): per-wave global atomics on the
-// few counters of list A serialise across the whole chip.
-constexpr unsigned BIN_BLOCKS = 1024;
-
-template <int PASS>
-__global__ __launch_bounds__(256) void k_bin(KArgs a, const int32_t* ids, uint32_t mask) {
-  __shared__ int s_cnt[NEDF_MAX_OBJECTS], s_base[NEDF_MAX_OBJECTS];
+// Pairs of list R: pixels with a valid ID whose object is in `mask`, as
+// (pixel, instance), after their counts per object (k_finalize or
+// k_clear_rgb): the workgroup counts its own pixels, reserves one range per
+// object and writes.  The first workgroup records the segments and the work
+// items over item_mask.
+__global__ __launch_bounds__(256) void k_bin_write(KArgs a, const int32_t* ids, uint32_t mask) {
+  __shared__ int s_cnt[NEDF_MAX_OBJECTS], s_base[NEDF_MAX_OBJECTS], s_seg[NEDF_MAX_OBJECTS], s_lim[NEDF_MAX_OBJECTS];
   const int t = threadIdx.x, lane = t & 63;
-  const int64_t per = ((a.n_rays + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+  const int64_t per = bin_span(a.n_rays, gridDim.x);
   const int64_t p0 = int64_t(blockIdx.x) * per;
   const int64_t p1 = p0 + per < a.n_rays ? p0 + per : a.n_rays;
-  PairList* L = &a.C->A;
-  if (t < NEDF_MAX_OBJECTS) s_cnt[t] = 0;
+  PairList* L = &a.C->R;
+  if (t < 64) {
+    const int64_t c = t < a.n_obj ? L->cnt[t] : 0;
+    int64_t total;
+    const int64_t off = wave_prefix(c, t, total);
+    const int64_t o0 = min(off, a.capacity), lim = min(off + c, a.capacity) - o0;
+    if (t < NEDF_MAX_OBJECTS) {
+      s_seg[t] = int(o0);
+      s_lim[t] = int(lim);
+      s_cnt[t] = 0;
+    }
+    if (blockIdx.x == 0) {
+      const bool counted = t < a.n_obj && ((a.item_mask >> t) & 1u);
+      int items, pairs;
+      wave_prefix(counted ? int((lim + a.item_pairs - 1) / a.item_pairs) : 0, t, items);
+      wave_prefix(counted ? int(lim) : 0, t, pairs);
+      if (t <= a.n_obj) L->off[t] = int(o0);
+      if (t < a.n_obj) L->cnt[t] = int(lim);
+      if (t == 0) {
+        a.C->last_pairs = pairs;
+        a.C->last_items = items;
+        if (total > a.capacity) set_status(a.status, NEDF_ERR_CAPACITY);
+      }
+    }
+  }
   __syncthreads();
-  // traversal 0 counts; in pass 1 traversal 1 writes
-  for (int trav = 0; trav <= PASS; ++trav) {
-    for (int64_t pb = p0; pb < p1; pb += 256) {
-      const int64_t p = pb + t;
-      const int inst = p < p1 ? ids[p] : -1;
-      const int obj = inst >= 0 && inst < a.n_inst ? a.inst_object[inst] : -1;
-      const bool want = obj >= 0 && obj < a.n_obj && ((mask >> obj) & 1u);
-      uint64_t pending = __ballot(want);
-      while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int o = __shfl(obj, leader);
-        const uint64_t match = __ballot(want && obj == o);
-        int off = 0;
-        if (lane == leader) off = atomicAdd(&s_cnt[o], __popcll(match));
-        if (trav == 1) {
-          off = __shfl(off, leader);
-          if (want && obj == o) {
-            const int pos = s_base[o] + off + __popcll(match & ((1ull << lane) - 1ull));
-            if (pos < L->cnt[o]) a.pairs[L->off[o] + pos] = make_uint2(uint32_t(p), uint32_t(inst));
-          }
-        }
-        pending &= ~match;
-      }
-    }
-    __syncthreads();
-    if (t < a.n_obj) {
-      const int c = s_cnt[t];
-      if (PASS == 0) {
-        if (c) atomicAdd(&L->cnt[t], c);
-      } else if (trav == 0) {
-        s_base[t] = c ? atomicAdd(&L->fill[t], c) : 0;
-        s_cnt[t] = 0;
-      }
-    }
-    __syncthreads();
+  for (int64_t pb = p0; pb < p1; pb += 256) {
+    const int64_t p = pb + t;
+    bin_groups(a, p < p1 ? ids[p] : -1, mask, lane, [&](int o, uint64_t match, bool) {
+      if (lane == __ffsll((unsigned long long)match) - 1) atomicAdd(&s_cnt[o], __popcll(match));
+    });
+  }
+  __syncthreads();
+  if (t < a.n_obj) {
+    s_base[t] = s_cnt[t] ? atomicAdd(&L->fill[t], s_cnt[t]) : 0;
+    s_cnt[t] = 0;
+  }
+  __syncthreads();
+  for (int64_t pb = p0; pb < p1; pb += 256) {
+    const int64_t p = pb + t;
+    const int inst = p < p1 ? ids[p] : -1;
+    bin_groups(a, inst, mask, lane, [&](int o, uint64_t match, bool mine) {
+      const int leader = __ffsll((unsigned long long)match) - 1;
+      int off = 0;
+      if (lane == leader) off = atomicAdd(&s_cnt[o], __popcll(match));
+      off = __shfl(off, leader);
+      const int pos = s_base[o] + off + __popcll(match & ((1ull << lane) - 1ull));
+      if (mine && pos < s_lim[o]) a.pairs[s_seg[o] + pos] = make_uint2(uint32_t(p), uint32_t(inst));
+    });
   }
 }
 
@@ -119,7 +110,7 @@ struct Secant {
 };
 
 __global__ void k_refine_analytic(KArgs a, uint32_t mask) {
-  const PairList* L = &a.C->A;
+  const PairList* L = &a.C->R;
   for (int m = 0; m < a.n_obj; ++m) {
     if (!((mask >> m) & 1u)) continue;
     const ObjDesc od = a.obj[m];
@@ -161,17 +152,18 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_refine_mlp(KArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t lds[eng::NBUF * eng::slot_bytes(CHUNK, SBX)];
   __shared__ int s_item;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  PairList* PL = &a.C->A;
+  __shared__ ItemTable s_tab;
+  build_items(a, s_tab, 32 * NW);
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
+    if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
     __syncthreads();
     const int item = s_item;
     __syncthreads();
-    if (item >= PL->total_items) break;
-    const int obj = item_object(PL, a.n_obj, item);
-    const int local = (item - PL->item_start[obj]) * (32 * NW) + wave * 32 + (lane & 31);
-    const bool valid = local < PL->cnt[obj];
-    const uint2 pr = a.pairs[PL->off[obj] + (valid ? local : 0)];
+    if (item >= s_tab.total) break;
+    const int obj = item_object(s_tab, a.n_obj, item);
+    const int local = (item - s_tab.start[obj]) * (32 * NW) + wave * 32 + (lane & 31);
+    const bool valid = local < s_tab.cnt[obj];
+    const uint2 pr = a.pairs[s_tab.off[obj] + (valid ? local : 0)];
     const ObjDesc& od = a.obj[obj];
     const uint8_t* blob = od.blob;
     const nedf_blob_header* hb = reinterpret_cast<const nedf_blob_header*>(blob);
@@ -216,18 +208,38 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_refine_mlp(KArgs a) {
 }
 
 // ---- deferred shading ---------------------------------------------------------
-__global__ void k_clear_rgb(KArgs a, const int32_t* ids) {
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= a.n_rays) return;
-  const int inst = ids[p];
-  float c[3] = {a.clear_rgb[0], a.clear_rgb[1], a.clear_rgb[2]};
-  if (inst >= 0 && inst < a.n_inst) {
-    const ObjDesc& od = a.obj[a.inst_object[inst]];
-    if (od.field != NEDF_FIELD_MLP) { c[0] = od.param[3]; c[1] = od.param[4]; c[2] = od.param[5]; }
+// Clear colour (or an analytic object's own colour) of every pixel; with BIN
+// the hit pixels per object of `mask` are counted for k_bin_write.
+template <bool BIN>
+__global__ __launch_bounds__(256) void k_clear_rgb(KArgs a, const int32_t* ids, uint32_t mask) {
+  __shared__ int s_cnt[NEDF_MAX_OBJECTS];
+  const int t = threadIdx.x, lane = t & 63;
+  if (BIN && t < NEDF_MAX_OBJECTS) s_cnt[t] = 0;
+  if (BIN) __syncthreads();
+  const int64_t per = bin_span(a.n_rays, gridDim.x);
+  const int64_t p0 = int64_t(blockIdx.x) * per;
+  const int64_t p1 = p0 + per < a.n_rays ? p0 + per : a.n_rays;
+  for (int64_t pb = p0; pb < p1; pb += 256) {
+    const int64_t p = pb + t;
+    const int inst = p < p1 ? ids[p] : -1;
+    if (p < p1) {
+      float c[3] = {a.clear_rgb[0], a.clear_rgb[1], a.clear_rgb[2]};
+      if (inst >= 0 && inst < a.n_inst) {
+        const ObjDesc& od = a.obj[a.inst_object[inst]];
+        if (od.field != NEDF_FIELD_MLP) { c[0] = od.param[3]; c[1] = od.param[4]; c[2] = od.param[5]; }
+      }
+      a.rgb[3 * p + 0] = c[0];
+      a.rgb[3 * p + 1] = c[1];
+      a.rgb[3 * p + 2] = c[2];
+    }
+    if constexpr (BIN) bin_groups(a, inst, mask, lane, [&](int o, uint64_t match, bool) {
+      if (lane == __ffsll((unsigned long long)match) - 1) atomicAdd(&s_cnt[o], __popcll(match));
+    });
   }
-  a.rgb[3 * p + 0] = c[0];
-  a.rgb[3 * p + 1] = c[1];
-  a.rgb[3 * p + 2] = c[2];
+  if constexpr (BIN) {
+    __syncthreads();
+    if (t < a.n_obj && s_cnt[t]) atomicAdd(&a.C->R.cnt[t], s_cnt[t]);
+  }
 }
 
 // NeRF shading: a wave shades 32 / K pixels with K samples each; trunk with
@@ -249,22 +261,23 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_shade(KArgs a) {
   const int K = a.shade_K;  // 1, 2, 4, 8, 16 or 32
   const int ppw = 32 / K;
   const int slot = lane & 31, q = slot / K, j = slot % K;
-  // first pass: the binned pixels (list A), outliers pushed to list B;
-  // second pass (chord mode): list B
+  // first pass: the binned pixels (list R), outliers pushed to the same
+  // segments of list B; second pass (chord mode): list B
   const bool chord = a.shade_chord != 0;
-  PairList* PL = chord ? &a.C->B : &a.C->A;
   const uint2* prs_list = chord ? a.pairsB : a.pairs;
   PairList* RS = &a.C->B;
+  __shared__ ItemTable s_tab;
+  build_items(a, s_tab, ppw * NW);
   for (;;) {
-    if (threadIdx.x == 0) s_item = atomicAdd(&PL->work_counter, 1);
+    if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
     __syncthreads();
     const int item = s_item;
     __syncthreads();
-    if (item >= PL->total_items) break;
-    const int obj = item_object(PL, a.n_obj, item);
-    const int local = (item - PL->item_start[obj]) * (ppw * NW) + wave * ppw + q;
-    const bool valid = local < PL->cnt[obj];
-    const uint2 pr = prs_list[PL->off[obj] + (valid ? local : 0)];
+    if (item >= s_tab.total) break;
+    const int obj = item_object(s_tab, a.n_obj, item);
+    const int local = (item - s_tab.start[obj]) * (ppw * NW) + wave * ppw + q;
+    const bool valid = local < s_tab.cnt[obj];
+    const uint2 pr = prs_list[s_tab.off[obj] + (valid ? local : 0)];
     const ObjDesc& od = a.obj[obj];
     const uint8_t* blob = od.blob;
     const nedf_blob_header* hb = reinterpret_cast<const nedf_blob_header*>(blob);
@@ -351,7 +364,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_shade(KArgs a) {
           atomicAdd(&a.C->stats[1], __popcll(m));
         }
         base = __shfl(base, leader);
-        if (outlier) a.pairsB[RS->off[obj] + base + __popcll(m & ((1ull << lane) - 1ull))] = pr;
+        if (outlier) a.pairsB[s_tab.off[obj] + base + __popcll(m & ((1ull << lane) - 1ull))] = pr;
       }
     }
     if (valid && half == 0 && j == 0) {
@@ -421,17 +434,6 @@ __global__ void k_composite(KArgs a, const float* shadow, float* rgb) {
   rgb[3 * p + 2] *= f;
 }
 
-int cu_count2() {
-  static int ncu = 0;
-  if (ncu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      ncu = 256;
-  }
-  return ncu;
-}
-
 unsigned grid_n(int64_t n) {
   const int64_t g = (n + 255) / 256;
   return unsigned(g > 0 ? g : 1);
@@ -439,37 +441,34 @@ unsigned grid_n(int64_t n) {
 
 }  // namespace
 
-// Bins hit pixels of the objects in `mask` into list A with work items of
-// `per` pixels.
-void stage_bin_pixels(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t mask, int per) {
+void stage_bin_write(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t mask, uint32_t item_mask, int per) {
   KArgs k = k0;
-  k.item_mask = mask;
+  k.item_mask = item_mask;
   k.item_pairs = per;
-  k.L = &k.C->A;
-  const unsigned g = grid_n(k.n_rays) < BIN_BLOCKS ? grid_n(k.n_rays) : BIN_BLOCKS;
-  hipLaunchKernelGGL(k_zero_list, dim3(1), dim3(256), 0, s, &k.C->A);
-  hipLaunchKernelGGL(k_bin<0>, dim3(g), dim3(256), 0, s, k, ids, mask);
-  hipLaunchKernelGGL(k_scan_pixels, dim3(1), dim3(64), 0, s, k);
-  hipLaunchKernelGGL(k_bin<1>, dim3(g), dim3(256), 0, s, k, ids, mask);
+  hipLaunchKernelGGL(k_bin_write, dim3(bin_blocks(k.n_rays)), dim3(256), 0, s, k, ids, mask);
 }
 
-void stage_refine(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t mlp_mask, uint32_t sphere_mask,
+void stage_refine(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t mlp_mask, uint32_t sphere_mask,
                   int dtype) {
   prof_mark("infer.refine", s, true);
-  if (sphere_mask) {
-    stage_bin_pixels(k, s, ids, sphere_mask, 1);
-    hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
-  }
+  KArgs k = k0;
+  k.lcnt = k.C->R.cnt;
+  k.loff = k.C->R.off;
+  k.lwork = &k.C->R.work_counter;
+  k.item_mask = mlp_mask;
+  // BF16: one workgroup of 8 waves per CU, which streams each weight chunk
+  // into LDS once for 256 samples (two workgroups of 4 waves stream it
+  // twice; the refinement is bound by that L2 -> LDS stream, and the 8-wave
+  // form measured 8 % faster on the 1080p frame); FP32: one of 4 waves
+  const int nw = dtype == NEDF_BF16 ? 8 : 4;
+  // both kinds in one binning; the counters report the networks' items
+  stage_bin_write(k, s, ids, mlp_mask | sphere_mask, mlp_mask ? mlp_mask : sphere_mask, mlp_mask ? 32 * nw : 1);
+  if (sphere_mask) hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
   if (mlp_mask) {
-    // BF16: one workgroup of 8 waves per CU, which streams each weight chunk
-    // into LDS once for 256 samples (two workgroups of 4 waves stream it
-    // twice; the refinement is bound by that L2 -> LDS stream, and the 8-wave
-    // form measured 8 % faster on the 1080p frame); FP32: one of 4 waves
-    stage_bin_pixels(k, s, ids, mlp_mask, dtype == NEDF_BF16 ? 32 * 8 : 32 * 4);
     if (dtype == NEDF_BF16)
-      hipLaunchKernelGGL((k_refine_mlp<1, 256, 8, 10, 2, 1, 8>), dim3(cu_count2()), dim3(512), 0, s, k);
+      hipLaunchKernelGGL((k_refine_mlp<1, 256, 8, 10, 2, 1, 8>), dim3(cu_count()), dim3(512), 0, s, k);
     else
-      hipLaunchKernelGGL((k_refine_mlp<0, 256, 8, 10, eng::sb_default<0>(), 1, 4>), dim3(cu_count2()), dim3(256), 0,
+      hipLaunchKernelGGL((k_refine_mlp<0, 256, 8, 10, eng::sb_default<0>(), 1, 4>), dim3(cu_count()), dim3(256), 0,
                          s, k);
   }
   prof_mark("infer.refine", s, false);
@@ -478,59 +477,33 @@ void stage_refine(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t ml
 namespace {
 void launch_shade(const KArgs& k, hipStream_t s, int dtype) {
   if (dtype == NEDF_BF16)
-    hipLaunchKernelGGL((k_shade<1, 256, 8, 10, 4, 128, 2, 1, 8>), dim3(cu_count2()), dim3(512), 0, s, k);
+    hipLaunchKernelGGL((k_shade<1, 256, 8, 10, 4, 128, 2, 1, 8>), dim3(cu_count()), dim3(512), 0, s, k);
   else
-    hipLaunchKernelGGL((k_shade<0, 256, 8, 10, 4, 128, eng::sb_default<0>(), 1, 4>), dim3(cu_count2()), dim3(256),
+    hipLaunchKernelGGL((k_shade<0, 256, 8, 10, 4, 128, eng::sb_default<0>(), 1, 4>), dim3(cu_count()), dim3(256),
                        0, s, k);
 }
 }  // namespace
 
-// List B takes the outliers of the first shading pass in the segments of
-// list A (an object's outliers are a subset of its pixels); its counts and the
-// resampling count start at zero.
-__global__ void k_rs_prepare(KArgs a) {
-  const int m = threadIdx.x;
-  PairList* A = &a.C->A;
-  PairList* B = &a.C->B;
-  if (m <= a.n_obj) B->off[m] = A->off[m];
-  if (m < a.n_obj) {
-    B->cnt[m] = 0;
-    B->fill[m] = 0;
-  }
-  if (m == 0) {
-    B->total_items = B->work_counter = B->total_pairs = 0;
-    a.C->stats[1] = 0;
-  }
-}
-
-// Work items of the outlier list (segments fixed by k_rs_prepare).
-__global__ void k_rs_items(KArgs a) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  PairList* L = &a.C->B;
-  int items = 0, total = 0;
-  for (int m = 0; m < a.n_obj; ++m) {
-    L->item_start[m] = items;
-    const int c = L->cnt[m];
-    if ((a.item_mask >> m) & 1u) items += (c + a.item_pairs - 1) / a.item_pairs;
-    total += c;
-  }
-  L->item_start[a.n_obj] = items;
-  L->total_items = items;
-  L->total_pairs = total;
-  L->work_counter = 0;
-}
-
-void stage_shade(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t nerf_mask, int dtype, int rs_samples) {
+void stage_shade(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t nerf_mask, int dtype, int rs_samples) {
   prof_mark("shade", s, true);
-  hipLaunchKernelGGL(k_clear_rgb, dim3(grid_n(k.n_rays)), dim3(256), 0, s, k, ids);
+  KArgs k = k0;
+  const dim3 g(bin_blocks(k.n_rays));
+  // list R takes the hit pixels; list B the outliers of the first pass in
+  // the segments of list R (an object's outliers are a subset of its pixels)
+  hipLaunchKernelGGL(k_begin_pixels, dim3(1), dim3(64), 0, s, k, nerf_mask && rs_samples > 0 ? 1 : 0);
+  if (nerf_mask) hipLaunchKernelGGL(k_clear_rgb<true>, g, dim3(256), 0, s, k, ids, nerf_mask);
+  else hipLaunchKernelGGL(k_clear_rgb<false>, g, dim3(256), 0, s, k, ids, nerf_mask);
   if (nerf_mask) {
     // BF16: one workgroup of 8 waves per CU sharing each weight copy; FP32: 4 waves
     const int nw = dtype == NEDF_BF16 ? 8 : 4;
-    stage_bin_pixels(k, s, ids, nerf_mask, (32 / k.shade_K) * nw);
+    stage_bin_write(k, s, ids, nerf_mask, nerf_mask, (32 / k.shade_K) * nw);
+    k.item_mask = nerf_mask;
+    k.loff = k.C->R.off;
+    k.lcnt = k.C->R.cnt;
+    k.lwork = &k.C->R.work_counter;
     KArgs k1 = k;
     k1.shade_chord = 0;
-    if (rs_samples > 0) hipLaunchKernelGGL(k_rs_prepare, dim3(1), dim3(NEDF_MAX_OBJECTS + 64), 0, s, k1);
-    else k1.rs_sigma = 0.0f;
+    if (rs_samples <= 0) k1.rs_sigma = 0.0f;
     launch_shade(k1, s, dtype);
     if (rs_samples > 0) {
       // second pass: the outliers, volume-rendered over the bounding chord
@@ -538,9 +511,8 @@ void stage_shade(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t ner
       KArgs k2 = k;
       k2.shade_chord = 1;
       k2.shade_K = rs_samples;
-      k2.item_mask = nerf_mask;
-      k2.item_pairs = (32 / rs_samples) * nw;
-      hipLaunchKernelGGL(k_rs_items, dim3(1), dim3(64), 0, s, k2);
+      k2.lcnt = k.C->B.cnt;
+      k2.lwork = &k.C->B.work_counter;
       launch_shade(k2, s, dtype);
       prof_mark("shade.resample", s, false);
     }

@@ -25,21 +25,24 @@ struct RaySrcHost {
 };
 
 // A per-object list of (ray or pixel, instance) pairs in the workspace:
-// object m owns pairs[off[m] .. off[m] + cnt[m]); item_start is the prefix of
-// work items over the objects a stage processes.
+// object m owns pairs[off[m] .. off[m] + cnt[m]).
 struct PairList {
   int32_t cnt[NEDF_MAX_OBJECTS];
   int32_t fill[NEDF_MAX_OBJECTS];
   int32_t off[NEDF_MAX_OBJECTS + 1];
-  int32_t item_start[NEDF_MAX_OBJECTS + 1];
-  int32_t total_items, work_counter, total_pairs, pad;
+  int32_t work_counter;
 };
 
 // Device counters in the workspace (after the 256-byte status block).
 struct WsCounters {
-  PairList A;       // primary pairs (culling result) / binned pixels
-  PairList B;       // fallback pairs (NeDF uncertain rays)
-  PairList S;       // pairs of the current depth slab of the network stage
+  PairList A;       // primary pairs (culling result)
+  PairList B;       // fallback pairs (NeDF uncertain rays); fill: those left after the depth test
+  PairList R;       // pixels binned by object (refinement, shading)
+  // pairs of the current depth slab of the network stage, in the segments of
+  // list A: slab k counts in set k % 2 while its filter clears the other set
+  int32_t slab_cnt[2][NEDF_MAX_OBJECTS];
+  int32_t slab_work[2];
+  int32_t last_pairs, last_items;  // of the list binned last
   int32_t stats[8]; // [0] pairs decided by the network, [1] sent to the marcher, [2] network misses,
                     // [3] marcher pairs left after the depth test, [4] pairs after culling
   uint32_t dmin_bits, dmax_bits;  // range of the pairs' lowest possible depths (float bits, >= 0)
@@ -71,6 +74,28 @@ bool refine_supported(int dtype, const nedf_mlp_shape& s);
 
 struct KArgs;
 
+// Initial value of NEDF_TUNE_SLABS: the number of depth slabs is chosen by
+// the size of the call.
+constexpr int NEDF_SLABS_DEFAULT = 8;
+
+int cu_count();
+
+// Launch shape of the 256-wide BF16/FP8 kernels from the tuning table: value
+// 100 * (32-row blocks per wave - 1) + 10 * occupancy + superchunk (blocks
+// sharing each weight read, workgroups per CU, chunks per copy); other shapes
+// use one block, one workgroup per CU and the default superchunk.  The grid
+// is persistent: one workgroup per CU and occupancy level.
+// Tuning value of the matrix-core kernels: 1000 * (workgroup waves / 4 - 1) +
+// 100 * (row blocks per wave - 1) + 10 * workgroups per CU + chunks per
+// superchunk.
+
+inline int tune_waves(int v) { return v >= 1000 ? 8 : 4; }
+
+// Matrix-core marcher over the list in k (objects in its item_mask).
+void launch_march(const KArgs& k, hipStream_t s, int dtype, int W);
+// Regression-form intersection networks over the list in k; v: launch shape.
+void launch_nedf(const KArgs& k, hipStream_t s, int dtype, int v);
+
 // Stages (kernels enqueued on s, no host synchronisation).
 void stage_init_cull(const KArgs& k, hipStream_t s, uint32_t item_mask, int item_pairs);
 void stage_march(const KArgs& k, hipStream_t s, bool list_b, uint32_t analytic_mask, int dtype, int W, int H,
@@ -82,14 +107,19 @@ void stage_nedf(const KArgs& k, hipStream_t s, int dtype, uint32_t nedf_mask, in
 // Classifier-form networks (NEDF_IN_POINTS16) over the current slab list.
 void launch_nedf_cls(const KArgs& k, hipStream_t s, int dtype);
 bool nedf_cls_supported(int dtype, const nedf_mlp_shape& s);
-void stage_finalize(const KArgs& k, hipStream_t s);
+// Keys -> depth / id; with a nonzero bin_mask the hit pixels of those objects
+// are counted for the binning that follows (stage_bin_write).
+void stage_finalize(const KArgs& k, hipStream_t s, uint32_t bin_mask = 0);
 constexpr int MAX_KEY_SETS = 8;
 struct KeySets {
   const uint64_t* p[MAX_KEY_SETS];
   int32_t n;
 };
 void stage_merge_keys(const KArgs& k, hipStream_t s, const KeySets& ks);
-void stage_bin_pixels(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t mask, int per);
+// Second half of the binning of hit pixels into list R: the pairs, after
+// their counts per object; item_mask and per describe the work items that
+// the counters report.
+void stage_bin_write(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t mask, uint32_t item_mask, int per);
 void stage_refine(const KArgs& k, hipStream_t s, const int32_t* ids, uint32_t mlp_mask, uint32_t sphere_mask,
                   int dtype);
 // rs_samples > 0: pixels whose density stays below k.rs_sigma at every one of

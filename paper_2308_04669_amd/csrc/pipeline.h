@@ -24,10 +24,13 @@ struct KArgs {
   int32_t item_pairs;    // pairs per work item of that stage
   int* status;
   WsCounters* C;
-  PairList* L;           // list the current stage reads
-  uint2* pairs;          // its pair array
-  PairList* LB;          // second list (fallback)
-  uint2* pairsB;
+  // list the current stage reads: counts and segment offsets per object, the
+  // counter its work items are claimed from, and its pair array
+  const int32_t* lcnt;
+  const int32_t* loff;
+  int32_t* lwork;
+  uint2* pairs;
+  uint2* pairsB;         // fallback list
   uint2* pairsS;         // depth-slab list of the network stage
   float* pair_dm;        // per pair of list A: lowest depth it can report (world units)
   uint8_t* pair_slab;    // per pair of list A: its depth slab (network stage)
@@ -102,11 +105,87 @@ __device__ __forceinline__ void emit_key(const KArgs& a, uint32_t ray, uint32_t 
   atomicMin(reinterpret_cast<unsigned long long*>(&a.keys[ray]), (unsigned long long)pack_key(D, gid));
 }
 
-// Work item -> (object, first pair) of list L (items of `per` pairs).
-__device__ __forceinline__ int item_object(const PairList* L, int n_obj, int item) {
+// Work items of the list a stage reads, formed by every workgroup for itself
+// from the counts in the workspace (one wave, one scan over the at most 32
+// objects): a launch of its own for this prefix would cost more than all
+// workgroups repeating it, since each launch waits for the one before
+// (4-5 us each; the depth pass of a 64 x 64 frame was mostly such launches).
+struct ItemTable {
+  int32_t start[NEDF_MAX_OBJECTS + 1];  // first work item of each object
+  int32_t cnt[NEDF_MAX_OBJECTS];
+  int32_t off[NEDF_MAX_OBJECTS];
+  int32_t total;
+};
+
+// Exclusive prefix of v over the lanes of a wave (lanes 0..63) and its total.
+template <class I>
+__device__ __forceinline__ I wave_prefix(I v, int lane, I& total) {
+  I incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const I y = __shfl_up(incl, o);
+    if (lane >= o) incl += y;
+  }
+  total = __shfl(incl, 63);
+  return incl - v;
+}
+
+// Called by the whole workgroup; ends with a barrier.
+__device__ __forceinline__ void build_items(const KArgs& a, ItemTable& t, int per) {
+  if (threadIdx.x < 64) {
+    const int m = threadIdx.x;
+    const int c = m < a.n_obj ? a.lcnt[m] : 0;
+    const int items = m < a.n_obj && ((a.item_mask >> m) & 1u) ? (c + per - 1) / per : 0;
+    int total;
+    const int start = wave_prefix(items, m, total);
+    if (m <= NEDF_MAX_OBJECTS) t.start[m] = start;
+    if (m < NEDF_MAX_OBJECTS) {
+      t.cnt[m] = c;
+      t.off[m] = m < a.n_obj ? a.loff[m] : 0;
+    }
+    if (m == 0) t.total = total;
+  }
+  __syncthreads();
+}
+
+// Object of work item `item`.
+__device__ __forceinline__ int item_object(const ItemTable& t, int n_obj, int item) {
   int obj = 0;
-  while (obj + 1 < n_obj && L->item_start[obj + 1] <= item) ++obj;
+  while (obj + 1 < n_obj && t.start[obj + 1] <= item) ++obj;
   return obj;
+}
+
+// ---- binning of pixels by object --------------------------------------------
+// A workgroup takes a contiguous range of pixels and aggregates its counts
+// per object in LDS (lanes of a wave grouped by object, one LDS atomic per
+// group), so global atomics are one per (workgroup, object): per-wave global
+// atomics on the few counters of a list serialise across the whole chip.
+constexpr unsigned BIN_BLOCKS = 1024;
+
+inline unsigned bin_blocks(int64_t n_rays) {
+  const int64_t g = (n_rays + 255) / 256;
+  return unsigned(g < 1 ? 1 : g > int64_t(BIN_BLOCKS) ? int64_t(BIN_BLOCKS) : g);
+}
+
+// Pixels of each workgroup.
+__device__ __forceinline__ int64_t bin_span(int64_t n_rays, unsigned blocks) {
+  return ((n_rays + blocks - 1) / blocks + 255) / 256 * 256;
+}
+
+// Calls f(object, lanes, whether this lane is one of them) for every object
+// of `mask` among the wave's instances (inst < 0: none); whole wave active.
+template <class F>
+__device__ __forceinline__ void bin_groups(const KArgs& a, int inst, uint32_t mask, int lane, F&& f) {
+  const int obj = inst >= 0 && inst < a.n_inst ? a.inst_object[inst] : -1;
+  const bool want = obj >= 0 && obj < a.n_obj && ((mask >> obj) & 1u);
+  uint64_t pending = __ballot(want);
+  while (pending) {
+    const int o = __shfl(obj, __ffsll((unsigned long long)pending) - 1);
+    const bool mine = want && obj == o;
+    const uint64_t match = __ballot(mine);
+    f(o, match, mine);
+    pending &= ~match;
+  }
 }
 
 }  // namespace nedf
