@@ -351,20 +351,24 @@ __device__ __forceinline__ uint64_t pack_key(float depth, int id) {
 __device__ __forceinline__ void set_status(int* ws_status, int code) { atomicMax(ws_status, code); }
 
 // Analytic signed distances of the SDF-biased shapes (must match the
-// generator's shape list: sphere, rounded box, torus, ellipsoid).
+// generator's shape list: sphere, rounded box, torus, ellipsoid).  The sums
+// of squares are written as the fused operations they compile to, in one
+// order: left to the compiler, the order depends on the code around a call,
+// and two kernels of one stage would differ in the last bit.
+__device__ __forceinline__ float norm3(float x, float y, float z) { return sqrtf(fmaf(z, z, fmaf(x, x, y * y))); }
 __device__ __forceinline__ float sdf_shape(int shape, float x, float y, float z) {
-  if (shape == 0) return sqrtf(x * x + y * y + z * z) - 0.6f;
+  if (shape == 0) return norm3(x, y, z) - 0.6f;
   if (shape == 1) {
     const float qx = fabsf(x) - 0.4f, qy = fabsf(y) - 0.4f, qz = fabsf(z) - 0.4f;
     const float mx = fmaxf(qx, 0.f), my = fmaxf(qy, 0.f), mz = fmaxf(qz, 0.f);
-    return sqrtf(mx * mx + my * my + mz * mz) + fminf(fmaxf(qx, fmaxf(qy, qz)), 0.f) - 0.05f;
+    return norm3(mx, my, mz) + fminf(fmaxf(qx, fmaxf(qy, qz)), 0.f) - 0.05f;
   }
   if (shape == 2) {
-    const float qx = sqrtf(x * x + z * z) - 0.5f;
-    return sqrtf(qx * qx + y * y) - 0.2f;
+    const float qx = sqrtf(fmaf(x, x, z * z)) - 0.5f;
+    return sqrtf(fmaf(y, y, qx * qx)) - 0.2f;
   }
   const float ax = x / 0.7f, ay = y / 0.45f, az = z / 0.35f;
   const float bx = x / 0.49f, by = y / 0.2025f, bz = z / 0.1225f;
-  const float k0 = sqrtf(ax * ax + ay * ay + az * az), k1 = sqrtf(bx * bx + by * by + bz * bz);
+  const float k0 = norm3(ax, ay, az), k1 = norm3(bx, by, bz);
   return k1 > 0.f ? k0 * (k0 - 1.0f) / k1 : -0.35f;
 }

@@ -58,7 +58,6 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const uint32_t stash = eng::lds_offset(s_stash) + 16u * threadIdx.x;
   __shared__ ItemTable s_tab;  // the current depth slab
-  PairList* FBL = &a.C->B;
   build_items(a, s_tab, 32 * NW);
   const int total = s_tab.total;
   if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
@@ -66,7 +65,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   int item = s_item;
   int cur = 0;
   bool primed = false;
-  int n_hit = 0, n_fb = 0, n_miss = 0;
+  int n_route[3] = {0, 0, 0};
   while (item < total) {
     __syncthreads();
     if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
@@ -229,29 +228,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
     const float mu = l * (float(cell) * (1.0f / 4096.0f) - 1.0f);
     const float pp = sigmoidf_(alpha_hat);
     const float D = __uint_as_float(sv.w) * (__uint_as_float(sv.z) - mu);
-    const bool mine = valid_s && half == 0;
-    const bool to_fb = mine && (inside_s || (pp >= a.p_lo && pp <= a.p_hi));
-    const bool hit = mine && !to_fb && pp > a.p_hi && D > 0.0f;
-    if (hit) emit_key(a, prs.x, prs.y, D);
-    const uint64_t m = __ballot(to_fb);
-    if (m) {
-      const int leader = __ffsll((unsigned long long)m) - 1;
-      int base = 0;
-      if (lane == leader) base = atomicAdd(&FBL->cnt[obj], __popcll(m));
-      base = __shfl(base, leader);
-      if (to_fb) a.pairsB[FBL->off[obj] + base + __popcll(m & ((1ull << lane) - 1ull))] = prs;
-    }
-    const uint64_t mh = __ballot(hit), mv = __ballot(mine);
-    n_hit += __popcll(mh);
-    n_fb += __popcll(m);
-    n_miss += __popcll(mv) - __popcll(mh) - __popcll(m);
+    route_pairs(a, obj, s_tab.off[obj], prs, valid_s && half == 0, inside_s, pp, D, lane, n_route);
     item = next;
   }
-  if (lane == 0 && (n_hit | n_fb | n_miss)) {
-    atomicAdd(&a.C->stats[0], n_hit);
-    atomicAdd(&a.C->stats[1], n_fb);
-    atomicAdd(&a.C->stats[2], n_miss);
-  }
+  flush_routing(a, lane, n_route);
 }
 
 }  // namespace

@@ -701,6 +701,16 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
+Kernels choose_kernels(KArgs& k, int dtype, int per, int most, int64_t bound) {
+  k.split_per = 0;
+  if (dtype == NEDF_F32) return {true, false};
+  if ((bound + per - 1) / per + k.n_obj <= most) return {true, false};
+  if (k.n_rays > (int64_t(1) << 20)) return {false, true};
+  k.split_per = per;
+  k.split_max = most;
+  return {true, true};
+}
+
 int cu_count() {
   static int ncu = 0;
   if (ncu == 0) {
@@ -790,7 +800,10 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   }
   if (W > 0) {
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, true);
-    launch_march(k, s, dtype, W);
+    Kernels kn{false, true};
+    if (W == 256) kn = choose_kernels(k, dtype, 1, 4 * cu_count(), pair_bound(k));
+    if (kn.small) launch_march_small(k, s, dtype, cu_count());
+    if (kn.large) launch_march(k, s, dtype, W);
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, false);
   }
 }
@@ -822,7 +835,13 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, i
     }
     prof_mark("net", s, true);
     if (classifier) launch_nedf_cls(k, s, dtype);
-    else launch_nedf(k, s, dtype, v);
+    else {
+      Kernels kn{false, true};
+      if (dtype == NEDF_F32 || (dtype == NEDF_BF16 && n_slabs == 1))
+        kn = choose_kernels(k, dtype, 32, 3 * cu_count(), pair_bound(k));
+      if (kn.small) launch_nedf_small(k, s, dtype, cu_count());
+      if (kn.large) launch_nedf(k, s, dtype, v);
+    }
     prof_mark("net", s, false);
   }
   prof_mark("infer.nedf", s, false);

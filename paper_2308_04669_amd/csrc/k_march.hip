@@ -1,4 +1,6 @@
-// The plain volume-rendering marcher (Eq. 5) on MLP density fields.
+// The plain volume-rendering marcher (Eq. 5) on MLP density fields: BF16, and
+// the 64-wide FP32 network (256-wide FP32 lists of any length run on the
+// feature-split kernel).
 #include "pipeline.h"
 #include "runtime.h"
 
@@ -23,7 +25,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_march_mlp(KArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int N = a.n_samples;
   const int n_chunks = (N + SPC - 1) / SPC;
-  build_items(a, s_tab, NW);
+  if (!build_items(a, s_tab, NW)) return;
   const int total = s_tab.total;
   // one item of lookahead: the next item is claimed during the current
   // item's last pass so that its weights stream in behind this one's
@@ -56,7 +58,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_march_mlp(KArgs a) {
     }
     const float delta = (tb - ta) / float(N);
     const float pa[3] = {fmaf(ta, dl[0], ol[0]), fmaf(ta, dl[1], ol[1]), fmaf(ta, dl[2], ol[2])};
-    float carry = 0.f, carry_c = 0.f, sw = 0.f, sw_c = 0.f, swt = 0.f, swt_c = 0.f;
+    MarchSum sum;
     int next = total;
     for (int c = 0; c < n_chunks; ++c) {
       const bool last = c + 1 == n_chunks;
@@ -90,32 +92,10 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_march_mlp(KArgs a) {
         const float u = partial[nb][0] + __shfl_xor(partial[nb][0], 32) + head_b;
         float v = mlp_sigma(od, u, p[0], p[1], p[2]) * delta;
         if (lane >= 32 || si >= N || !seg) v = 0.f;
-        // inclusive scan of optical depth over the wave (sample order = lane order)
-        float incl = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const float y = __shfl_up(incl, off);
-          if (lane >= off) incl += y;
-        }
-        const float tau = (carry + carry_c) + (incl - v);
-        const float w = expf(-tau) * one_minus_exp_neg(v);
-        float ws = w, wts = w * (ta + tr);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-          ws += __shfl_xor(ws, off);
-          wts += __shfl_xor(wts, off);
-        }
-        // a block wholly past the last sample adds exact zeros
-        neu_add(sw, sw_c, ws);
-        neu_add(swt, swt_c, wts);
-        neu_add(carry, carry_c, __shfl(incl, 63));
+        sum.add(v, ta + tr, lane);
       }
     }
-    if (lane == 0 && valid && seg) {
-      const float A = sw + sw_c;
-      if (A >= a.hit_thr && A > 0.0f) emit_key(a, pr.x, pr.y, g.s * ((swt + swt_c) / A));
-      atomicMax(&a.opac[pr.x], __float_as_uint(fmaxf(A, 0.0f)));
-    }
+    if (lane == 0 && valid && seg) sum.emit(a, pr, g.s);
     item = next;
   }
 }
@@ -149,8 +129,7 @@ void launch_march(const KArgs& k, hipStream_t s, int dtype, int W) {
     if (W == 256) launch_march_mlp<1, 256, 8, 10>(k, s);
     else launch_march_mlp<1, 64, 3, 6>(k, s);
   } else {
-    if (W == 256) launch_march_mlp<0, 256, 8, 10>(k, s);
-    else launch_march_mlp<0, 64, 3, 6>(k, s);
+    launch_march_mlp<0, 64, 3, 6>(k, s);
   }
 }
 

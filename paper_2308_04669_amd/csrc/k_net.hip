@@ -1,5 +1,6 @@
 // The NeDF intersection network (Eq. 1, 2, 7) in its regression form, with
-// routing of uncertain pairs to the marcher.
+// routing of uncertain pairs to the marcher: BF16, FP8 and MX FP8 (FP32 lists
+// of any length run on the feature-split kernel).
 #include "pipeline.h"
 #include "runtime.h"
 
@@ -26,8 +27,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const uint32_t stash = eng::lds_offset(s_stash) + 16u * threadIdx.x;
   __shared__ ItemTable s_tab;  // the current depth slab
-  PairList* FB = &a.C->B;
-  build_items(a, s_tab, PPW * NW);
+  if (!build_items(a, s_tab, PPW * NW)) return;
   const int total = s_tab.total;
   if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
   __syncthreads();
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
   int slot = 0;
   bool primed = false;
   // routing counts, per wave, flushed once at the end
-  int n_hit = 0, n_fb = 0, n_miss = 0;
+  int n_route[3] = {0, 0, 0};
   while (item < total) {
     // claim the next item now so that its weights stream in behind this pass
     __syncthreads();
@@ -91,31 +91,11 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
       const float z = partial[nb][1] + __shfl_xor(partial[nb][1], 32) + hbias[1];
       const float p = sigmoidf_(z);
       const float D = __uint_as_float(st.w) * (__uint_as_float(st.z) - l * fminf(fmaxf(mu_hat, -1.0f), 1.0f));
-      const bool mine = valid_s && half == 0;
-      const bool to_fb = mine && (inside_s || (p >= a.p_lo && p <= a.p_hi));
-      const bool hit = mine && !to_fb && p > a.p_hi && D > 0.0f;
-      if (hit) emit_key(a, prs.x, prs.y, D);
-      // wave-aggregated push into the object's segment of list B
-      const uint64_t m = __ballot(to_fb);
-      if (m) {
-        const int leader = __ffsll((unsigned long long)m) - 1;
-        int base = 0;
-        if (lane == leader) base = atomicAdd(&FB->cnt[obj], __popcll(m));
-        base = __shfl(base, leader);
-        if (to_fb) a.pairsB[FB->off[obj] + base + __popcll(m & ((1ull << lane) - 1ull))] = prs;
-      }
-      const uint64_t mh = __ballot(hit), mv = __ballot(mine);
-      n_hit += __popcll(mh);
-      n_fb += __popcll(m);
-      n_miss += __popcll(mv) - __popcll(mh) - __popcll(m);
+      route_pairs(a, obj, s_tab.off[obj], prs, valid_s && half == 0, inside_s, p, D, lane, n_route);
     }
     item = next;
   }
-  if (lane == 0 && (n_hit | n_fb | n_miss)) {
-    atomicAdd(&a.C->stats[0], n_hit);
-    atomicAdd(&a.C->stats[1], n_fb);
-    atomicAdd(&a.C->stats[2], n_miss);
-  }
+  flush_routing(a, lane, n_route);
 }
 
 template <int DT>
@@ -146,19 +126,15 @@ void launch_nedf_net(const KArgs& k, hipStream_t s, int v) {
     // MX: superchunks of four blocks; eight waves (items of 256 pairs) or four
     if (v >= 1000) hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 8>), g1, b8, 0, s, k);
     else hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 4>), g1, b4, 0, s, k);
-  } else {
-    hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 4>), g1, b4, 0, s, k);
   }
 }
 
 }  // namespace
 
-void launch_nedf(const KArgs& k0, hipStream_t s, int dtype, int v) {
-  KArgs k = k0;
+void launch_nedf(const KArgs& k, hipStream_t s, int dtype, int v) {
   if (dtype == NEDF_FP8) launch_nedf_net<2>(k, s, v);
   else if (dtype == NEDF_FP8_MX) launch_nedf_net<3>(k, s, v);
-  else if (dtype == NEDF_BF16) launch_nedf_net<1>(k, s, v);
-  else launch_nedf_net<0>(k, s, v);
+  else launch_nedf_net<1>(k, s, v);
 }
 
 }  // namespace nedf

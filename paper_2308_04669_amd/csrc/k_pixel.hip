@@ -1,6 +1,7 @@
 // Per-pixel stages after the depth buffer: binning hit pixels by object,
 // secant refinement of the winning depth, deferred shading (Eq. 8, Alg. 1
 // step 2), shadow rays and the shadow multiplier (Alg. 2), composite.
+#include <algorithm>
 #include <cstring>
 
 #include "pipeline.h"
@@ -85,30 +86,6 @@ __global__ __launch_bounds__(256) void k_bin_write(KArgs a, const int32_t* ids, 
   }
 }
 
-// ---- secant refinement --------------------------------------------------------
-// f(t) = surface function at the local point of world depth t; seeds D -/+ h,
-// `steps` secant updates with a [D - 2h, D + 2h] guard (needs steps + 1
-// evaluations; the last iterate is not evaluated).
-struct Secant {
-  float t0, t1, f0, f1, out, lo, hi;
-  bool active;
-  __device__ void start(float D, float h) {
-    t0 = D - h; t1 = D + h; out = D; lo = D - 2.f * h; hi = D + 2.f * h;
-  }
-  __device__ float update() {  // returns the new iterate (evaluation point)
-    const float den = f1 - f0;
-    bool ok = active && den != 0.0f;
-    const float tn = ok ? t1 - f1 * (t1 - t0) / den : t1;
-    ok = ok && tn >= lo && tn <= hi;
-    if (ok) out = tn;
-    active = ok;
-    return tn;
-  }
-  __device__ void shift(float tn, float fn) {
-    if (active) { t0 = t1; f0 = f1; t1 = tn; f1 = fn; }
-  }
-};
-
 __global__ void k_refine_analytic(KArgs a, uint32_t mask) {
   const PairList* L = &a.C->R;
   for (int m = 0; m < a.n_obj; ++m) {
@@ -153,7 +130,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_refine_mlp(KArgs a) {
   __shared__ int s_item;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   __shared__ ItemTable s_tab;
-  build_items(a, s_tab, 32 * NW);
+  if (!build_items(a, s_tab, 32 * NW)) return;
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
     __syncthreads();
@@ -456,20 +433,19 @@ void stage_refine(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t m
   k.loff = k.C->R.off;
   k.lwork = &k.C->R.work_counter;
   k.item_mask = mlp_mask;
-  // BF16: one workgroup of 8 waves per CU, which streams each weight chunk
-  // into LDS once for 256 samples (two workgroups of 4 waves stream it
-  // twice; the refinement is bound by that L2 -> LDS stream, and the 8-wave
-  // form measured 8 % faster on the 1080p frame); FP32: one of 4 waves
+  // long BF16 lists: one workgroup of 8 waves per CU, which streams each
+  // weight chunk into LDS once for 256 samples (two workgroups of 4 waves
+  // stream it twice; the refinement is bound by that L2 -> LDS stream, and the
+  // 8-wave form measured 8 % faster on the 1080p frame)
   const int nw = dtype == NEDF_BF16 ? 8 : 4;
   // both kinds in one binning; the counters report the networks' items
   stage_bin_write(k, s, ids, mlp_mask | sphere_mask, mlp_mask ? mlp_mask : sphere_mask, mlp_mask ? 32 * nw : 1);
   if (sphere_mask) hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
   if (mlp_mask) {
-    if (dtype == NEDF_BF16)
+    const Kernels kn = choose_kernels(k, dtype, 32, 3 * cu_count(), std::min<int64_t>(k.capacity, k.n_rays));
+    if (kn.small) launch_refine_small(k, s, dtype, cu_count());
+    if (kn.large)
       hipLaunchKernelGGL((k_refine_mlp<1, 256, 8, 10, 2, 1, 8>), dim3(cu_count()), dim3(512), 0, s, k);
-    else
-      hipLaunchKernelGGL((k_refine_mlp<0, 256, 8, 10, eng::sb_default<0>(), 1, 4>), dim3(cu_count()), dim3(256), 0,
-                         s, k);
   }
   prof_mark("infer.refine", s, false);
 }

@@ -91,6 +91,27 @@ int cu_count();
 
 inline int tune_waves(int v) { return v >= 1000 ? 8 : 4; }
 
+// The same stages for short lists (k_small.hip): 256-wide, eight-layer
+// networks in F32 or BF16 with `grid` workgroups.
+void launch_nedf_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid);
+void launch_march_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid);
+void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid);
+
+// Sets up k for the choice between a stage's two kernels and says which to
+// launch: BF16 lists of at most `most` units of `per` pairs go to the small
+// one, FP32 lists always.  `most` is where the two take equal time: three
+// rounds of 32-pair units on the chip (3 x 10 us against 31 us for the one
+// round of the large kernel), four rounds of marched pairs (4 x 40 us against
+// its 4 serial passes of 38 us).
+// `bound` is the host's bound on the pairs; if it does not decide, both are
+// launched and the device's counts decide (the other ends at once, about
+// 4 us), except in calls of more than 2^20 rays, where such a list would save
+// less than that launch costs every other call.
+struct Kernels {
+  bool small, large;
+};
+Kernels choose_kernels(KArgs& k, int dtype, int per, int most, int64_t bound);
+
 // Matrix-core marcher over the list in k (objects in its item_mask).
 void launch_march(const KArgs& k, hipStream_t s, int dtype, int W);
 // Regression-form intersection networks over the list in k; v: launch shape.

@@ -30,6 +30,7 @@ struct KArgs {
   const int32_t* loff;
   int32_t* lwork;
   uint2* pairs;
+  int32_t split_per, split_max;  // choice between a stage's two kernels (build_items)
   uint2* pairsB;         // fallback list
   uint2* pairsS;         // depth-slab list of the network stage
   float* pair_dm;        // per pair of list A: lowest depth it can report (world units)
@@ -114,7 +115,7 @@ struct ItemTable {
   int32_t start[NEDF_MAX_OBJECTS + 1];  // first work item of each object
   int32_t cnt[NEDF_MAX_OBJECTS];
   int32_t off[NEDF_MAX_OBJECTS];
-  int32_t total;
+  int32_t total, mine;
 };
 
 // Exclusive prefix of v over the lanes of a wave (lanes 0..63) and its total.
@@ -130,8 +131,16 @@ __device__ __forceinline__ I wave_prefix(I v, int lane, I& total) {
   return incl - v;
 }
 
-// Called by the whole workgroup; ends with a barrier.
-__device__ __forceinline__ void build_items(const KArgs& a, ItemTable& t, int per) {
+// Which of a stage's two kernels takes the list: the register-resident one
+// (ROUTE_LARGE) or the feature-split one (ROUTE_SMALL), by the number of
+// split_per-pair units in the list against split_max, on the device, where
+// the counts are; 0 (no split_per): the stage has launched one kernel only.
+enum { ROUTE_LARGE = 0, ROUTE_SMALL = 1 };
+
+// Called by the whole workgroup; ends with a barrier.  False if the list is
+// the other kernel's (uniform over the grid).
+template <int ROUTE = ROUTE_LARGE>
+__device__ __forceinline__ bool build_items(const KArgs& a, ItemTable& t, int per) {
   if (threadIdx.x < 64) {
     const int m = threadIdx.x;
     const int c = m < a.n_obj ? a.lcnt[m] : 0;
@@ -144,8 +153,12 @@ __device__ __forceinline__ void build_items(const KArgs& a, ItemTable& t, int pe
       t.off[m] = m < a.n_obj ? a.loff[m] : 0;
     }
     if (m == 0) t.total = total;
+    int units = 0;
+    if (a.split_per) wave_prefix(items ? (c + a.split_per - 1) / a.split_per : 0, m, units);
+    if (m == 0) t.mine = !a.split_per || (units <= a.split_max) == (ROUTE == ROUTE_SMALL);
   }
   __syncthreads();
+  return t.mine != 0;
 }
 
 // Object of work item `item`.
@@ -154,6 +167,93 @@ __device__ __forceinline__ int item_object(const ItemTable& t, int n_obj, int it
   while (obj + 1 < n_obj && t.start[obj + 1] <= item) ++obj;
   return obj;
 }
+
+// Optical depth and weights of one pair, 32 samples at a time in order, one
+// per lane (lanes 32..63 pass v = 0): the scan runs across the wave, the sums
+// over chunks are Neumaier-compensated.
+struct MarchSum {
+  float carry = 0.f, carry_c = 0.f, sw = 0.f, sw_c = 0.f, swt = 0.f, swt_c = 0.f;
+  // v: optical depth of this lane's sample, t: its local depth
+  __device__ __forceinline__ void add(float v, float t, int lane) {
+    // inclusive scan of optical depth over the wave (sample order = lane order)
+    float incl = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const float y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    const float tau = (carry + carry_c) + (incl - v);
+    const float w = expf(-tau) * one_minus_exp_neg(v);
+    float ws = w, wts = w * t;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      ws += __shfl_xor(ws, off);
+      wts += __shfl_xor(wts, off);
+    }
+    // a block wholly past the last sample adds exact zeros
+    neu_add(sw, sw_c, ws);
+    neu_add(swt, swt_c, wts);
+    neu_add(carry, carry_c, __shfl(incl, 63));
+  }
+  // One lane of the pair's wave.
+  __device__ __forceinline__ void emit(const KArgs& a, uint2 pr, float s) const {
+    const float A = sw + sw_c;
+    if (A >= a.hit_thr && A > 0.0f) emit_key(a, pr.x, pr.y, s * ((swt + swt_c) / A));
+    atomicMax(&a.opac[pr.x], __float_as_uint(fmaxf(A, 0.0f)));
+  }
+};
+
+// Routing of the intersection network's pairs (one per lane of a half wave;
+// `mine` selects the lanes that hold one): confident hits to the key buffer,
+// uncertain pairs and origins inside the bounding sphere to the object's
+// segment of list B; n counts hits, fallbacks and misses.  Whole wave active.
+__device__ __forceinline__ void route_pairs(const KArgs& a, int obj, int seg_off, uint2 pr, bool mine, bool inside,
+                                            float p, float D, int lane, int (&n)[3]) {
+  const bool to_fb = mine && (inside || (p >= a.p_lo && p <= a.p_hi));
+  const bool hit = mine && !to_fb && p > a.p_hi && D > 0.0f;
+  if (hit) emit_key(a, pr.x, pr.y, D);
+  // wave-aggregated push into the object's segment of list B
+  const uint64_t m = __ballot(to_fb);
+  if (m) {
+    const int leader = __ffsll((unsigned long long)m) - 1;
+    int base = 0;
+    if (lane == leader) base = atomicAdd(&a.C->B.cnt[obj], __popcll(m));
+    base = __shfl(base, leader);
+    if (to_fb) a.pairsB[seg_off + base + __popcll(m & ((1ull << lane) - 1ull))] = pr;
+  }
+  const uint64_t mh = __ballot(hit), mv = __ballot(mine);
+  n[0] += __popcll(mh);
+  n[1] += __popcll(m);
+  n[2] += __popcll(mv) - __popcll(mh) - __popcll(m);
+}
+__device__ __forceinline__ void flush_routing(const KArgs& a, int lane, const int (&n)[3]) {
+  if (lane == 0 && (n[0] | n[1] | n[2]))
+    for (int i = 0; i < 3; ++i) atomicAdd(&a.C->stats[i], n[i]);
+}
+
+// ---- secant refinement --------------------------------------------------------
+// f(t) = surface function at the local point of world depth t; seeds D -/+ h,
+// `steps` secant updates with a [D - 2h, D + 2h] guard (needs steps + 1
+// evaluations; the last iterate is not evaluated).
+struct Secant {
+  float t0, t1, f0, f1, out, lo, hi;
+  bool active;
+  __device__ void start(float D, float h) {
+    t0 = D - h; t1 = D + h; out = D; lo = D - 2.f * h; hi = D + 2.f * h;
+  }
+  __device__ float update() {  // returns the new iterate (evaluation point)
+    const float den = f1 - f0;
+    bool ok = active && den != 0.0f;
+    const float tn = ok ? t1 - f1 * (t1 - t0) / den : t1;
+    ok = ok && tn >= lo && tn <= hi;
+    if (ok) out = tn;
+    active = ok;
+    return tn;
+  }
+  __device__ void shift(float tn, float fn) {
+    if (active) { t0 = t1; f0 = f1; t1 = tn; f1 = fn; }
+  }
+};
 
 // ---- binning of pixels by object --------------------------------------------
 // A workgroup takes a contiguous range of pixels and aggregates its counts
