@@ -1,8 +1,10 @@
 // Device layout of an intersection network's training state: float32 master
 // weights and biases, Adam moments, last-step gradients and bfloat16 copies
-// of every weight matrix for the matrix-core GEMMs, [N][Kpad] and transposed
-// [Kpad][N] (K padded to a multiple of 64 with zeros).  Layer i is [N][K] row-major (PyTorch layout); layers
-// 0..n_hidden-1 are the hidden layers, layer n_hidden the head.  A
+// of every weight matrix but the regression form's head, W [N][Kpad] and its
+// transpose [Kpad][N] (K padded to a multiple of 128 with zeros), packed as
+// matrix-core fragments (nedf_train_frag).  Layer i is [N][K] row-major
+// (PyTorch layout); layers 0..n_hidden-1 are the hidden layers, layer
+// n_hidden the head.  A
 // classifier-form network (NEDF_IN_POINTS16) has the head, two layers per
 // residual block and the tail, whose 193 rows are kept as 256 (rows past
 // Nsrc stay zero: their gradients are zero).
@@ -26,6 +28,31 @@ struct nedf_train_layout {
   nedf_train_layer L[NEDF_TRAIN_MAX_LAYERS];
   size_t total;
 };
+
+// Place (in bfloat16 values) of element (row, k) of a packed matrix of ks
+// K-steps of 16: fragments of 32 rows x 16 k, lane l holding row l % 32 and
+// k = 8 (l / 32) .. + 7.  Fragments lie [row block][K-step], or, for a matrix
+// whose K-steps are consumed outermost (the classifier head, 256 rows),
+// [K-step / 4][row block][K-step % 4].
+static inline
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+size_t nedf_train_frag(int row, int k, int ks, int k_outer) {
+  const int fb = row / 32, s = k / 16;
+  const size_t frag = k_outer ? size_t(s / 4) * 32 + fb * 4 + s % 4 : size_t(fb) * ks + s;
+  return (frag * 64 + row % 32 + 32 * ((k % 16) / 8)) * 8 + k % 8;
+}
+
+// Row of a 32 x 32 tile of the arrays kept for the weight gradients at which
+// sample r of 32 lies: samples 8 c + j, j = 0..7, lie 4 rows apart, so that
+// the 8 x 8 blocks that the weight gradients transpose are loaded as whole
+// 256-byte runs.
+static inline
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+int nedf_train_tile_row(int r) { return (r >> 3) + 4 * (r & 7); }
 
 static inline size_t nedf_tl_align(size_t x) { return (x + 255) & ~size_t(255); }
 
