@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
       if (obf > bfv || (obf == bfv && oif < ifv)) { bfv = obf; ifv = oif; }
     }
     const float alpha_hat = st[0][4];  // lane half 0 holds the hit logit
-    eng::u32x4 sv = eng::lds_read16<0>(stash), d1 = sv, d2 = sv, d3 = sv;
-    eng::lds_wait4<0>(sv, d1, d2, d3);
+    eng::u32x4 sv = eng::lds_read16<0>(stash);
+    eng::lds_wait1<0>(sv);
     const uint2 prs = make_uint2(sv.x & 0x7FFFFFFFu, sv.y & 0x7FFFFFFFu);
     const bool valid_s = (sv.x >> 31) != 0, inside_s = (sv.y >> 31) != 0;
     // S^-1 (Eq. 4): mu = l ((128 c + f) / 4096 - 1), exact up to the final product

@@ -83,8 +83,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
     primed = next_blob != nullptr;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      eng::u32x4 st = eng::lds_read16<0>(stash + uint32_t(nb) * (16u * NT)), d1 = st, d2 = st, d3 = st;
-      eng::lds_wait4<0>(st, d1, d2, d3);
+      eng::u32x4 st = eng::lds_read16<0>(stash + uint32_t(nb) * (16u * NT));
+      eng::lds_wait1<0>(st);
       const uint2 prs = make_uint2(st.x & 0x7FFFFFFFu, st.y & 0x7FFFFFFFu);
       const bool valid_s = (st.x >> 31) != 0, inside_s = (st.y >> 31) != 0;
       const float mu_hat = partial[nb][0] + __shfl_xor(partial[nb][0], 32) + hbias[0];
