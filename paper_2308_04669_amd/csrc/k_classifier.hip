@@ -40,9 +40,15 @@ struct ClsCfg {
   static constexpr int HDMA = HCB + 128;
   static_assert(HCB == 32768, "head chunk layout");
   static_assert(HDMA <= SLOT, "head chunk copy must fit an LDS slot");
-  static_assert(eng::dma_instr(HDMA) == eng::dma_instr(SCB1), "uniform copy count in the head loop");
+  static_assert(eng::dma_instr(HDMA, 4) == eng::dma_instr(SCB1, 4) && eng::dma_instr(HDMA, 8) == eng::dma_instr(SCB1, 8),
+                "uniform copy count in the head loop");
 };
 
+// Bound by the matrix cores: 8 waves keep two on each SIMD, so that one's
+// epilogues and encodings lie under the other's products (0.81 -> 1.06
+// PFLOP/s in BF16; registers just suffice, with the bins and copy addresses
+// out of them).  4 waves serve FP32 (a wave needs the registers of two) and
+// lists of one round of 128-pair items, which they finish in 0.7 of the time.
 template <int DT, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   using C = ClsCfg<DT>;
@@ -58,7 +64,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const uint32_t stash = eng::lds_offset(s_stash) + 16u * threadIdx.x;
   __shared__ ItemTable s_tab;  // the current depth slab
-  build_items(a, s_tab, 32 * NW);
+  if (!build_items<NW == 8 ? ROUTE_LARGE : ROUTE_SMALL>(a, s_tab, 32 * NW)) return;
   const int total = s_tab.total;
   if (threadIdx.x == 0) s_item = atomicAdd(a.lwork, 1);
   __syncthreads();
@@ -196,6 +202,9 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
     for (int b = 0; b < nblk; ++b) {
       const uint8_t* w1 = hid + size_t(2 * b) * hstride;
       const uint8_t* w2 = w1 + hstride;
+      // opaque, so that the loop keeps no per-lane copy address of its own for
+      // every copy of the block (they spilled)
+      asm volatile("" : "+s"(w1), "+s"(w2));
       eng::layer<DT, 1, KSH, 8, C::CBH, C::CBH, KSH, 5, 0, C::CBH, 8, C::SBX, NW>(X, Tm, w1, w2, lds, cur, st);
       if (b + 1 < nblk)
         eng::layer<DT, 1, KSH, 8, C::CBH, C::CBH, KSH, 5, 3, C::CBH, 8, C::SBX, NW>(Tm, X, w2, w2 + hstride, lds, cur,
@@ -211,7 +220,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
         X, Tm, tail, next_head, lds, cur, st);
     primed = next_head != nullptr;
     // ---- both lane halves' maxima: the larger, or the lower bin on a tie
-    float bc = st[0][0], ic = st[0][1], bfv = st[0][2], ifv = st[0][3];
+    const float bin0 = half ? 4.f : 0.f;
+    float bc = st[0][0], ic = st[0][1] + bin0, bfv = st[0][2], ifv = st[0][3] + bin0;
     {
       const float obc = __shfl_xor(bc, 32), oic = __shfl_xor(ic, 32);
       if (obc > bc || (obc == bc && oic < ic)) { bc = obc; ic = oic; }
@@ -236,9 +246,12 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
 
 }  // namespace
 
-void launch_nedf_cls(const KArgs& k, hipStream_t s, int dtype) {
-  if (dtype == NEDF_BF16) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(cu_count()), dim3(256), 0, s, k);
-  else hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+void launch_nedf_cls(const KArgs& k0, hipStream_t s, int dtype, int64_t bound) {
+  KArgs k = k0;
+  const Kernels kn = choose_kernels(k, dtype, 128, cu_count(), bound);
+  if (dtype == NEDF_F32) hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+  else if (kn.small) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+  if (kn.large) hipLaunchKernelGGL((k_nedf_cls<1, 8>), dim3(cu_count()), dim3(512), 0, s, k);
 }
 
 }  // namespace nedf

@@ -834,7 +834,7 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, i
       else hipLaunchKernelGGL(k_slab_next, fg, dim3(256), 0, s, k0, slab);
     }
     prof_mark("net", s, true);
-    if (classifier) launch_nedf_cls(k, s, dtype);
+    if (classifier) launch_nedf_cls(k, s, dtype, pair_bound(k));
     else {
       Kernels kn{false, true};
       if (dtype == NEDF_F32 || (dtype == NEDF_BF16 && n_slabs == 1))

@@ -125,8 +125,11 @@ void stage_march(const KArgs& k, hipStream_t s, bool list_b, uint32_t analytic_m
 // slabs (objects in nedf_mask).
 void stage_nedf(const KArgs& k, hipStream_t s, int dtype, uint32_t nedf_mask, int n_slabs,
                 bool classifier = false);
-// Classifier-form networks (NEDF_IN_POINTS16) over the current slab list.
-void launch_nedf_cls(const KArgs& k, hipStream_t s, int dtype);
+// Classifier-form networks (NEDF_IN_POINTS16) over the current slab list; the
+// BF16 lists of one round of four-wave items go to that kernel, longer ones to
+// the eight-wave one (a round of it takes 1.4 times as long and holds twice
+// the pairs).  `bound`: the host's bound on the pairs.
+void launch_nedf_cls(const KArgs& k, hipStream_t s, int dtype, int64_t bound);
 bool nedf_cls_supported(int dtype, const nedf_mlp_shape& s);
 // Keys -> depth / id; with a nonzero bin_mask the hit pixels of those objects
 // are counted for the binning that follows (stage_bin_write).

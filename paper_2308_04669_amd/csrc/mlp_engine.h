@@ -377,18 +377,21 @@ __device__ __forceinline__ void epi_residual(int fb, const f32x16_t (&acc)[NB], 
 
 // Classifier epilogue: running first-maximum of the coarse bins (features
 // 0..63) and fine bins (64..191) of this lane's sample over its own
-// features, and the hit logit (feature 192).  st[nb] = {best coarse value,
-// its bin, best fine value, its bin, hit logit}; a lane's features increase
-// with r, so a strict comparison keeps the first maximum.
+// features, and the hit logit (feature 192, in lane half 0).  st[nb] = {best
+// coarse value, its bin, best fine value, its bin, hit logit}; a lane's
+// features increase with r, so a strict comparison keeps the first maximum.
+// The bins are those of lane half 0 (half 1: add 4), so that they are
+// literals: as lane values the compiler kept all 96 in registers across the
+// whole network.
 template <int NB, int NOUT>
 __device__ __forceinline__ void epi_argmax(int fb, const f32x16_t (&acc)[NB], float (&st)[NB][NOUT]) {
   static_assert(NOUT >= 5, "argmax state needs five values");
-  const int half = (threadIdx.x & 63) >> 5;
+  static_assert(NEDF_CLS_COARSE % 32 == 0 && NEDF_CLS_FINE % 32 == 0, "a block's rows are of one kind");
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int f = 32 * fb + 8 * (r / 4) + 4 * half + (r % 4);
+      const int f = 32 * fb + 8 * (r / 4) + (r % 4);
       const float v = acc[nb][r];
       if (f < NEDF_CLS_COARSE) {
         if (v > st[nb][0]) { st[nb][0] = v; st[nb][1] = float(f); }
