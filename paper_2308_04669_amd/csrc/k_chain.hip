@@ -29,34 +29,6 @@ __device__ __forceinline__ float from_hi(float x) {
   return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false)[1]);
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(x)), CTRL, 0xF, 0xF, true)));
-}
-
-// Sums each of 32 per-lane values over the 32 lanes of a half; lane l returns
-// the sum of v[l % 32].  Each step halves the values a lane carries.
-__device__ __forceinline__ float sum_scatter32(float (&v)[32], int lane) {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 16]), false, false);
-    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-  }
-  auto step = [&](auto nc, auto cc, bool up) __attribute__((always_inline)) {
-    constexpr int n = decltype(nc)::value;
-#pragma unroll
-    for (int i = 0; i < n; ++i) {
-      const float keep = up ? v[i + n] : v[i], send = up ? v[i] : v[i + n];
-      v[i] = keep + dpp<decltype(cc)::value>(send);
-    }
-  };
-  step(std::integral_constant<int, 8>{}, std::integral_constant<int, 0x128>{}, (lane & 8) != 0);  // row_ror:8
-  step(std::integral_constant<int, 4>{}, std::integral_constant<int, 0x141>{}, (lane & 4) != 0);  // row_half_mirror
-  step(std::integral_constant<int, 2>{}, std::integral_constant<int, 0x4E>{}, (lane & 2) != 0);   // quad_perm [2,3,0,1]
-  step(std::integral_constant<int, 1>{}, std::integral_constant<int, 0xB1>{}, (lane & 1) != 0);   // quad_perm [1,0,3,2]
-  return v[0];
-}
-
 // Regression form: encoding, the hidden layers, head, loss (Eq. 6) and the
 // data gradients of a workgroup's 32 NW rows.  N input components (6
 // Pluecker, 3 xyz), K0 K-steps of the first layer.
@@ -75,7 +47,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
   __shared__ __attribute__((aligned(16))) float s_bias[NEDF_MAX_LAYERS * 256];
   __shared__ __attribute__((aligned(16))) float s_head[2 * 256];
   __shared__ __attribute__((aligned(16))) float s_red[NW * 512];
-  __shared__ float s_row[NW][4], s_label[2][32 * NW];
+  __shared__ __attribute__((aligned(16))) float s_row[4][32 * NW];
+  __shared__ float s_label[2][32 * NW];
   constexpr int NT = 64 * NW;
   const int t = threadIdx.x, lane = t & 63, half = lane >> 5, wave = t >> 6;
   const size_t row = (size_t(blockIdx.x) * NW + wave) * 32 + (lane & 31);
@@ -244,33 +217,88 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
     v[2] = alpha * e * e;
     v[3] = fmaxf(y1, 0.f) + log1pf(expf(-fabsf(y1))) - alpha * y1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-      for (int off = 16; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off);
-      if (lane == 0) s_row[wave][q] = v[q];
-    }
-  }
-  // head weight gradients of the wave's rows, and G = (g_mu W_0 + g_z W_1) * (h > 0)
-  {
-#pragma unroll
     for (int q = 0; q < 4; ++q)
+      if (half == 0) s_row[q][32 * wave + lane] = v[q];
+  }
+  // head weight gradients, 64 features at a time: the wave's 32 x 64 values
+  // change places in the ring's free slot (16-byte chunk c of row r at c ^ (r
+  // % 8)), a lane adds two features over two groups of eight rows, and the
+  // groups of a 128-row tile are then added in order
+  {
+    uint8_t* const place = lds + chain::next_slot(chain::next_slot(cur)) * chain::SLOT + wave * 4096;
+    const int fp = lane & 31, r0 = 16 * half;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float v[32];
+    for (int q = 0; q < 4; ++q) {
+      const int r = lane & 31;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const u32x4 x = __builtin_bit_cast(u32x4, X[4 * q + m]);
-          const uint32_t w4[4] = {x.x, x.y, x.z, x.w};
+      for (int m = 0; m < 4; ++m)
+        *reinterpret_cast<u32x4*>(place + r * 128 + 16 * ((2 * m + half) ^ (r & 7))) =
+            __builtin_bit_cast(u32x4, X[4 * q + m]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[8 * m + 2 * e] = (j ? g1 : g0) * bf_lo(w4[e]);
-            v[8 * m + 2 * e + 1] = (j ? g1 : g0) * bf_hi(w4[e]);
+      for (int g = 0; g < 2; ++g) {
+        float s[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, gr[2][8];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 8; i += 4) {
+            const float4 g4 = *reinterpret_cast<const float4*>(&s_row[j][32 * wave + r0 + 8 * g + i]);
+            gr[j][i] = g4.x;
+            gr[j][i + 1] = g4.y;
+            gr[j][i + 2] = g4.z;
+            gr[j][i + 3] = g4.w;
+          }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int rr = r0 + 8 * g + i;
+          const uint32_t w =
+              *reinterpret_cast<const uint32_t*>(place + rr * 128 + 16 * ((fp >> 2) ^ i) + 4 * (fp & 3));
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            s[j][0] = fmaf(gr[j][i], bf_lo(w), s[j][0]);
+            s[j][1] = fmaf(gr[j][i], bf_hi(w), s[j][1]);
           }
         }
-        const float s = sum_scatter32(v, lane);
-        // lane l % 32 holds K-step 4 q + (l % 32) / 8, feature 8 half + l % 8 of it
-        s_red[wave * 512 + j * 256 + 16 * (4 * q + ((lane & 31) >> 3)) + 8 * half + (lane & 7)] = s;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          *reinterpret_cast<float2*>(s_red + (4 * wave + 2 * half + g) * 128 + 64 * j + 2 * fp) =
+              make_float2(s[j][0], s[j][1]);
       }
+      __syncthreads();
+      for (int i = t; i < NW / 4 * 128; i += NT) {
+        const int tile = i >> 7, c = i & 127;
+        float acc = 0.f;
+#pragma unroll
+        for (int g = 0; g < 16; ++g) acc += s_red[(16 * tile + g) * 128 + c];
+        a.hpart[(size_t(blockIdx.x) * (NW / 4) + tile) * HEAD_PART + 256 * (c >> 6) + 64 * q + (c & 63)] = acc;
+      }
+      __syncthreads();
+    }
+  }
+  // a tile's bias gradients and loss sums: one wave, lane l adds rows l and
+  // l + 64, then a fixed butterfly
+  if (wave < NW / 4) {
+    const float invB = 1.0f / float(a.B);
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = s_row[q][128 * wave + lane] + s_row[q][128 * wave + lane + 64];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off);
+    }
+    if (lane == 0) {
+      float* P = a.hpart + (size_t(blockIdx.x) * (NW / 4) + wave) * HEAD_PART;
+      P[512] = v[0];
+      P[513] = v[1];
+      P[514] = (v[2] + a.w_hit * v[3]) * invB;
+      P[515] = v[2] * invB;
+      P[516] = v[3] * invB;
+    }
+  }
+  // G = (g_mu W_0 + g_z W_1) * (h > 0); h again from its packed words (kept
+  // unpacked from the dot products on, they spilled)
+#pragma unroll
+  for (int ks = 0; ks < 16; ++ks) asm volatile("" : "+v"(X[ks]));
+  {
     const float4* hw = reinterpret_cast<const float4*>(s_head);
     uint16_t* dst = G0 + size_t(NH - 1) * layer_elems;
 #pragma unroll
@@ -284,35 +312,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
       uint32_t o4[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float v0 = bf_lo(w4[e]) > 0.f ? fmaf(g0, wa[2 * e], g1 * wb[2 * e]) : 0.f;
-        const float v1 = bf_hi(w4[e]) > 0.f ? fmaf(g0, wa[2 * e + 1], g1 * wb[2 * e + 1]) : 0.f;
-        o4[e] = chain::pack2(v0, v1);
+        const float v0 = fmaf(g0, wa[2 * e], g1 * wb[2 * e]);
+        const float v1 = fmaf(g0, wa[2 * e + 1], g1 * wb[2 * e + 1]);
+        // a positive half has its sign bit clear and is not zero (h >= 0)
+        o4[e] = chain::pack2(v0, v1) & chain::select_mask(w4[e]);
       }
       const u32x4 g = {o4[0], o4[1], o4[2], o4[3]};
       X[ks] = __builtin_bit_cast(bf16x8_t, g);
       gstore(dst, row_off + kstep_off(ks), g);
-    }
-  }
-  __syncthreads();
-  {
-    // the workgroup's partials: waves in order
-    float* P = a.hpart + size_t(blockIdx.x) * HEAD_PART;
-    for (int i = t; i < 512; i += NT) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) s += s_red[w * 512 + i];
-      P[i] = s;
-    }
-    if (t == 0) {
-      const float invB = 1.0f / float(a.B);
-      float v[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int w = 0; w < NW; ++w)
-        for (int q = 0; q < 4; ++q) v[q] += s_row[w][q];
-      P[512] = v[0];
-      P[513] = v[1];
-      P[514] = (v[2] + a.w_hit * v[3]) * invB;
-      P[515] = v[2] * invB;
-      P[516] = v[3] * invB;
     }
   }
   // ---- data gradients: G_{l-1} = (G_l W_l) * (H_{l-1} > 0)

@@ -722,7 +722,7 @@ hipError_t launch_train_step(const nedf_mlp_shape& sh, uint8_t* st, const float*
   }
   float* hpart = reinterpret_cast<float*>(ws + off);
   const int waves = chain_line_waves(B, cu_count());
-  const int hblocks = B / (32 * waves);
+  const int hblocks = B / GT_BM;
   auto Hl = [&](int l) { return Hs + size_t(l) * B * W; };
   auto Gl = [&](int l) { return Gs + size_t(l) * B * W; };  // gradient at layer l's pre-activation
   auto F = [&](size_t o) { return reinterpret_cast<float*>(st + o); };

@@ -246,4 +246,9 @@ __device__ __forceinline__ uint32_t select_bits(uint32_t w, uint32_t m, int odd,
   return w & __builtin_bit_cast(uint32_t, t >> fifteen);
 }
 
+// Of a packed (non-negative) word's values: all ones where positive.
+__device__ __forceinline__ uint32_t select_mask(uint32_t w) {
+  return select_bits(0xFFFFFFFFu, positive_bits(w, 0, 0), 0, 0);
+}
+
 }  // namespace chain

@@ -24,7 +24,7 @@ struct ChainLineArgs {
   uint16_t* H;                         // [n_hidden][B][256] activations (the last one not written)
   uint16_t* G;                         // [n_hidden][B][256] gradients at the pre-activations
   uint8_t* bits;                       // [n_hidden][B / 32][4][64] words: signs of H (two blocks per lane)
-  float* hpart;                        // [workgroups][HEAD_PART]
+  float* hpart;                        // [B / 128][HEAD_PART]
 };
 
 struct ChainPointsArgs {
