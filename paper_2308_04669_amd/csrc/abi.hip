@@ -940,7 +940,7 @@ std::mutex g_tune_mu;
 // [kernel][dtype]: 10 * workgroups per CU + chunks per superchunk; for
 // NEDF_TUNE_SLABS the number of depth slabs of the network stage
 // (NEDF_SLABS_DEFAULT: chosen by the size of the call)
-int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 14}, {NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT}};
+int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 1014}, {NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT}};
 
 int tune_candidates(int kernel, int dtype, int32_t* out) {
   if (kernel < 0 || kernel > 2 || dtype < 0 || dtype > 2) return 0;
