@@ -7,6 +7,7 @@
 #include <cstring>
 
 #include "device_common.h"
+#include "mlp_engine.h"
 #include "runtime.h"
 #include "train_kernels.h"
 #include "train_layout.h"
@@ -90,85 +91,46 @@ __global__ void k_fp8_scales(const uint32_t* amax_w, const uint32_t* amax_a, int
   scales[2 * i + 1] = a > 0.f ? a / 448.0f : 1.0f;
 }
 
-// ---- GEMM ---------------------------------------------------------------------
-// C[M][N] = sum_k A(m, k) B(n, k) on 32x32x16 bf16 matrix cores with float32
-// accumulation.  A workgroup computes a 128 x BN tile with one wave per 64 x
-// 64 block (2 x 2 blocks of 32 x 32); K runs in stages of 64, staged in LDS as
-// [row][k] (k contiguous; rows padded to 72 elements, so that the 16-byte
-// fragment reads of a wave's 16-lane groups fall on distinct banks) and
-// double-buffered.  Global loads run two stages ahead of the matrix cores
-// (two register sets), so a stage's loads have two stages of multiplies to
-// arrive in.  Both operands are k-contiguous (KC: X[row][k], copied 16 bytes
-// at a time; BN = 256; the calibration's layers) or row-contiguous (RC:
-// X(k, row) in tiles, loaded as 8 x 8 blocks and transposed in registers by
-// byte permutes on the way to LDS; BN = 128; the weight gradients).  M is a
-// multiple of 128, N of BN and K of 128 per split.
-enum { KC = 0, RC = 1 };
-constexpr int GT_BM = 128, GT_BK = 64, GT_LD = 72;  // rows per tile, K stage, LDS row stride (bf16)
-// A stage row holds 8 chunks of 16 bytes.  LDS serves 16 lanes of a 16-byte
-// access per cycle over 64 banks; a row is 36 words (9 groups of 4 banks)
-// long, so the fragment reads (16 consecutive rows, one chunk: 9 j mod 16
-// distinct) are conflict-free.  The transposed stores of a row-contiguous
-// (RC) operand write rows 8 apart from 16 lanes (8 j mod 16: two groups, an
-// 8-way conflict), so there chunk c of row r sits at position
-// c ^ ((r / 16) % 8), which spreads them over 16 groups and keeps the reads
-// conflict-free; k-contiguous operands keep the plain layout.
-template <int LAYOUT>
-__device__ __forceinline__ int stage_chunk(int row, int chunk) {
-  return LAYOUT == RC ? chunk ^ ((row >> 4) & 7) : chunk;
-}
+// ---- GEMM of the calibration pass --------------------------------------------
+// out16[M][N] = relu(sum_k A(m, k) B(n, k) + bias[n]) on 32x32x16 bf16 matrix
+// cores with float32 accumulation, operands k-contiguous.  A workgroup
+// computes a 128 x 256 tile with one wave per 64 x 64 block (2 x 2 blocks of
+// 32 x 32); K runs in stages of 64, staged in LDS as [row][k] (rows padded to
+// 72 elements, so that the 16-byte fragment reads of a wave's 16-lane groups
+// fall on distinct banks) and double-buffered.  Global loads run two stages
+// ahead of the matrix cores (two register sets), so a stage's loads have two
+// stages of multiplies to arrive in.  The tile goes through LDS after the
+// last stage and leaves as whole 16-byte row pieces.  M is a multiple of 128,
+// N of 256 and K of 128.
+constexpr int GT_BM = 128, GT_BN = 256, GT_BK = 64, GT_LD = 72;  // tile, K stage, LDS row stride (bf16)
 
 struct GemmArgs {
   const uint16_t* A;
   const uint16_t* B;
   int M, N, K, lda, ldb;
-  int k_per_split;
-  // KC: out16 = relu(acc + bias[col]) [M][ldo]
   const float* bias;
-  uint16_t* out16;
+  uint16_t* out16;  // [M][ldo]
   int ldo;
-  // RC: part[split][M][N] float32 and the sums over k of A(m, k), colsum[split][M]
-  float* part;
-  float* colsum;
 };
 
-// 8 x 8 transpose of bfloat16: v[j] holds 8 consecutive rows at k = j; w[r]
-// gets the 8 values of row r in k order.
-__device__ __forceinline__ void transpose8x8(const uint4 (&v)[8], uint4 (&w)[8]) {
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const uint32_t sel = (r & 1) ? 0x07060302u : 0x05040100u;
-    uint32_t d[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      const uint32_t lo = reinterpret_cast<const uint32_t*>(&v[2 * p])[r >> 1];
-      const uint32_t hi = reinterpret_cast<const uint32_t*>(&v[2 * p + 1])[r >> 1];
-      d[p] = __builtin_amdgcn_perm(hi, lo, sel);
-    }
-    w[r] = make_uint4(d[0], d[1], d[2], d[3]);
-  }
-}
-
-// Register staging of one operand's stage (ROWS rows x 64 k) by NT threads.
-template <int LAYOUT, int ROWS, int NT>
-struct Stage;
 // Staging registers are plain 4 x 32-bit vectors (not the HIP vector
 // classes, which the compiler keeps in memory here).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Register staging of one operand's stage (ROWS rows x 64 k) by NT threads.
 template <int ROWS, int NT>
-struct Stage<KC, ROWS, NT> {
+struct Stage {
   static constexpr int PER = ROWS * 8 / NT;  // 16-byte chunks per thread
   u32x4 v[PER];
   // chunk c = t + NT i: row c / 8, k 8 (c % 8)
-  __device__ __forceinline__ void load(const uint16_t* X, int ld, int row0, int k0, int t, bool) {
+  __device__ __forceinline__ void load(const uint16_t* X, int ld, int row0, int k0, int t) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = t + NT * i;
       v[i] = *reinterpret_cast<const u32x4*>(X + size_t(row0 + (c >> 3)) * ld + k0 + 8 * (c & 7));
     }
   }
-  __device__ __forceinline__ void store(uint16_t* S, int t, bool, float*) const {
+  __device__ __forceinline__ void store(uint16_t* S, int t) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = t + NT * i;
@@ -176,87 +138,31 @@ struct Stage<KC, ROWS, NT> {
     }
   }
 };
-template <int ROWS, int NT>
-struct Stage<RC, ROWS, NT> {
-  // one 8 x 8 block per thread of the operand's half of the workgroup: rows
-  // 8 rb .. + 7, k chunk kb.  X lies in 32 x 32 tiles (k, row) in which k =
-  // 8 c + j is at c + 4 j, so that 16 lanes load 256 contiguous bytes
-  static_assert(ROWS == 128, "16 row blocks, 8 k chunks");
-  __device__ static __forceinline__ void place(int b, int& rb, int& kb) {
-    rb = (b & 3) + 4 * ((b >> 4) & 3);
-    kb = ((b >> 2) & 3) + 4 * (b >> 6);
-  }
-  uint4 v[8];
-  __device__ __forceinline__ void load(const uint16_t* X, int ld, int row0, int k0, int b, bool mine) {
-    if (!mine) return;
-    int rb, kb;
-    place(b, rb, kb);
-    const int row = row0 + 8 * rb;
-    const uint16_t* p = X + size_t(k0 / 32 + kb / 4) * (32 * size_t(ld)) + (row / 32) * 1024 + (kb % 4) * 32 + row % 32;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint4*>(p + 128 * j);
-  }
-  __device__ __forceinline__ void store(uint16_t* S, int b, bool mine, float* colsum8) const {
-    if (!mine) return;
-    int rb, kb;
-    place(b, rb, kb);
-    uint4 w[8];
-    transpose8x8(v, w);
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      *reinterpret_cast<uint4*>(S + (8 * rb + r) * GT_LD + 8 * stage_chunk<RC>(8 * rb + r, kb)) = w[r];
-      if (colsum8) {
-        const uint32_t* q = reinterpret_cast<const uint32_t*>(&w[r]);
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s += __uint_as_float(q[e] << 16) + __uint_as_float(q[e] & 0xFFFF0000u);
-        colsum8[r] += s;
-      }
-    }
-  }
-};
 
-// One output tile (bx, by) of split bz.
-template <int LAYOUT>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int bx, const int by, const int bz) {
-  constexpr int BM = GT_BM, BN = LAYOUT == KC ? 256 : 128;
-  constexpr int NT = BN * 2;            // threads: 2 x (BN / 64) waves
-  constexpr int WN = BN / 64;           // waves along N
-  constexpr int MI = BM / 64;           // 32-row blocks per wave (a wave takes BM / 2 rows)
+__global__ __launch_bounds__(512) void k_gemm(GemmArgs g) {
+  constexpr int BM = GT_BM, BN = GT_BN;
+  constexpr int NT = BN * 2;   // threads: 2 x (BN / 64) waves
+  constexpr int WN = BN / 64;  // waves along N
   constexpr int SA = BM * GT_LD, SB = BN * GT_LD;
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * (SA + SB)];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int m0 = bx * BM, n0 = by * BN;
-  const int kb = bz * g.k_per_split;
-  const int ke = min(g.K, kb + g.k_per_split);
-  const int n_stages = (ke - kb) / GT_BK;
-  // row-contiguous operands: A's blocks by threads 0..127, B's by 128..255
-  const int rc = t & 127;
-  const bool a_mine = LAYOUT == KC || t < 128;
-  const bool b_mine = LAYOUT == KC || t >= 128;
-  const int ts = LAYOUT == KC ? t : rc;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int n_stages = g.K / GT_BK;
   // two register sets, named (not indexed) so that they stay in registers
-  Stage<LAYOUT, BM, NT> ra0, ra1;
-  Stage<LAYOUT, BN, NT> rb0, rb1;
-  float cs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  f32x16_t acc[MI][2];
+  Stage<BM, NT> ra0, ra1;
+  Stage<BN, NT> rb0, rb1;
+  f32x16_t acc[2][2];
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x16_t{};
-  if (n_stages <= 0) return;  // never launched so (K a multiple of 64 per split)
-  ra0.load(g.A, g.lda, m0, kb, ts, a_mine);
-  rb0.load(g.B, g.ldb, n0, kb, ts, b_mine);
-  {
-    const int k1 = kb + min(1, n_stages - 1) * GT_BK;
-    ra1.load(g.A, g.lda, m0, k1, ts, a_mine);
-    rb1.load(g.B, g.ldb, n0, k1, ts, b_mine);
-  }
-  if (n_stages > 0) {
-    ra0.store(lds, ts, a_mine, LAYOUT == RC ? cs : nullptr);
-    rb0.store(lds + SA, ts, b_mine, nullptr);
-  }
+  ra0.load(g.A, g.lda, m0, 0, t);
+  rb0.load(g.B, g.ldb, n0, 0, t);
+  ra1.load(g.A, g.lda, m0, GT_BK, t);
+  rb1.load(g.B, g.ldb, n0, GT_BK, t);
+  ra0.store(lds, t);
+  rb0.store(lds + SA, t);
   __syncthreads();
   // one stage: multiply LDS buffer BUF; register set CUR (stage s, then
   // free) takes stage s + 2; set NXT (stage s + 1) goes to buffer BUF ^ 1.
@@ -267,122 +173,92 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int bx, const
     {                                                                                                     \
       /* unconditional (the last stage again past the end): a conditional */                            \
       /* load would keep the register set in memory */                                                    \
-      const int kl = kb + min((S_) + 2, n_stages - 1) * GT_BK;                                            \
-      RA_CUR.load(g.A, g.lda, m0, kl, ts, a_mine);                                                        \
-      RB_CUR.load(g.B, g.ldb, n0, kl, ts, b_mine);                                                        \
+      const int kl = min((S_) + 2, n_stages - 1) * GT_BK;                                                 \
+      RA_CUR.load(g.A, g.lda, m0, kl, t);                                                                 \
+      RB_CUR.load(g.B, g.ldb, n0, kl, t);                                                                 \
     }                                                                                                     \
-    const uint16_t* A_ = lds + (BUF) * (SA + SB) + (wm * (BM / 2) + (lane & 31)) * GT_LD;                  \
+    const uint16_t* A_ = lds + (BUF) * (SA + SB) + (wm * 64 + (lane & 31)) * GT_LD;                        \
     const uint16_t* B_ = lds + (BUF) * (SA + SB) + SA + (wn * 64 + (lane & 31)) * GT_LD;                   \
     _Pragma("unroll") for (int ks = 0; ks < GT_BK / 16; ++ks) {                                           \
-      bf16x8_t a[MI], b[2];                                                                               \
-      /* row 64 w + 32 i + lane % 32 (RC: 128-row tiles): (row / 16) % 8 = (4 w + 2 i + bit 4 of lane) % 8 */ \
-      const int c_ = 2 * ks + (lane >> 5), l4 = (lane >> 4) & 1;                                          \
-      _Pragma("unroll") for (int i = 0; i < MI; ++i) {                                                    \
-        const int ca = LAYOUT == RC ? c_ ^ ((4 * wm + 2 * i + l4) & 7) : c_;                                  \
-        a[i] = *reinterpret_cast<const bf16x8_t*>(A_ + 32 * i * GT_LD + 8 * ca);                          \
-      }                                                                                                   \
-      _Pragma("unroll") for (int i = 0; i < 2; ++i) {                                                     \
-        const int cb = LAYOUT == RC ? c_ ^ ((4 * wn + 2 * i + l4) & 7) : c_;                                  \
-        b[i] = *reinterpret_cast<const bf16x8_t*>(B_ + 32 * i * GT_LD + 8 * cb);                          \
-      }                                                                                                   \
-      _Pragma("unroll") for (int i = 0; i < MI; ++i)                                                      \
+      bf16x8_t a[2], b[2];                                                                                \
+      const int c_ = 2 * ks + (lane >> 5);                                                                \
+      _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                       \
+        a[i] = *reinterpret_cast<const bf16x8_t*>(A_ + 32 * i * GT_LD + 8 * c_);                          \
+      _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                       \
+        b[i] = *reinterpret_cast<const bf16x8_t*>(B_ + 32 * i * GT_LD + 8 * c_);                          \
+      _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                       \
       _Pragma("unroll") for (int j = 0; j < 2; ++j)                                                       \
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);              \
     }                                                                                                     \
     if ((S_) + 1 < n_stages) {                                                                            \
-      RA_NXT.store(lds + ((BUF) ^ 1) * (SA + SB), ts, a_mine, LAYOUT == RC ? cs : nullptr);                     \
-      RB_NXT.store(lds + ((BUF) ^ 1) * (SA + SB) + SA, ts, b_mine, nullptr);                              \
+      RA_NXT.store(lds + ((BUF) ^ 1) * (SA + SB), t);                                                     \
+      RB_NXT.store(lds + ((BUF) ^ 1) * (SA + SB) + SA, t);                                                \
     }                                                                                                     \
     __syncthreads();                                                                                      \
   }
   // operands swapped in the matrix-core call (B tile first): the accumulators
   // of lane l then hold row m = l % 32 of the block and, per group of four
   // registers, four consecutive columns
-  // the stage count is even (K a multiple of 128 per split), so both copies
-  // run every iteration
+  // the stage count is even, so both copies run every iteration
 #pragma unroll 1
   for (int s = 0; s < n_stages; s += 2) {
     NEDF_GEMM_STAGE(s, 0, ra0, rb0, ra1, rb1)
     NEDF_GEMM_STAGE(s + 1, 1, ra1, rb1, ra0, rb0)
   }
 #undef NEDF_GEMM_STAGE
-  // accumulator r of block (i, j): row 64 wm + 32 i + lane % 32, column
+  // bfloat16 tile in LDS ([128][BN + 8]), then 16-byte row pieces.
+  // Accumulator r of block (i, j): row 64 wm + 32 i + lane % 32, column
   // 64 wn + 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile
-  if constexpr (LAYOUT == RC) {
+  constexpr int LO = BN + 8;
+  static_assert(BM * LO <= 2 * (SA + SB), "output tile must fit the stage buffers");
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int row = m0 + wm * (BM / 2) + 32 * i + (lane & 31);
+  for (int i = 0; i < 2; ++i) {
+    const int r = wm * 64 + 32 * i + (lane & 31);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int col = n0 + wn * 64 + 32 * j + 8 * q + 4 * (lane >> 5);
-          *reinterpret_cast<float4*>(g.part + (size_t(bz) * g.M + row) * g.N + col) =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-        }
-    }
-    // column sums of A over this split's k, one set per m tile (written by
-    // the workgroups of the first n tile): the 8 threads of one row block
-    // (k chunks 0..7) combine in a fixed order
-    __shared__ float s_cs[128][8];
-    if (t < 128) {
-      int rb, kc;
-      Stage<RC, BM, NT>::place(rc, rb, kc);
+      for (int q = 0; q < 4; ++q) {
+        const int c = wn * 64 + 32 * j + 8 * q + 4 * (lane >> 5);
+        const float4 bb = *reinterpret_cast<const float4*>(g.bias + n0 + c);
+        const float v0 = fmaxf(acc[i][j][4 * q] + bb.x, 0.f), v1 = fmaxf(acc[i][j][4 * q + 1] + bb.y, 0.f);
+        const float v2 = fmaxf(acc[i][j][4 * q + 2] + bb.z, 0.f), v3 = fmaxf(acc[i][j][4 * q + 3] + bb.w, 0.f);
+        *reinterpret_cast<uint2*>(lds + r * LO + c) =
+            make_uint2(uint32_t(bf16_bits(v0)) | (uint32_t(bf16_bits(v1)) << 16),
+                       uint32_t(bf16_bits(v2)) | (uint32_t(bf16_bits(v3)) << 16));
+      }
+  }
+  __syncthreads();
+  constexpr int CH = BM * BN / 8;  // 16-byte pieces of the tile
 #pragma unroll
-      for (int r = 0; r < 8; ++r) s_cs[8 * rb + r][kc] = cs[r];
-    }
-    __syncthreads();
-    if (by == 0 && t < 128) {
-      float s_ = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) s_ += s_cs[t][q];
-      g.colsum[size_t(bz) * g.M + m0 + t] = s_;
-    }
-  } else {
-    // bfloat16 tile in LDS ([128][BN + 8]), then 16-byte row pieces
-    constexpr int LO = BN + 8;
-    static_assert(BM * LO <= 2 * (SA + SB), "output tile must fit the stage buffers");
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int r = wm * (BM / 2) + 32 * i + (lane & 31);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int c = wn * 64 + 32 * j + 8 * q + 4 * (lane >> 5);
-          const float4 bb = *reinterpret_cast<const float4*>(g.bias + n0 + c);
-          const float v0 = fmaxf(acc[i][j][4 * q] + bb.x, 0.f), v1 = fmaxf(acc[i][j][4 * q + 1] + bb.y, 0.f);
-          const float v2 = fmaxf(acc[i][j][4 * q + 2] + bb.z, 0.f), v3 = fmaxf(acc[i][j][4 * q + 3] + bb.w, 0.f);
-          *reinterpret_cast<uint2*>(lds + r * LO + c) =
-              make_uint2(uint32_t(bf16_bits(v0)) | (uint32_t(bf16_bits(v1)) << 16),
-                         uint32_t(bf16_bits(v2)) | (uint32_t(bf16_bits(v3)) << 16));
-        }
-    }
-    __syncthreads();
-    constexpr int CH = BM * BN / 8;  // 16-byte pieces of the tile
-#pragma unroll
-    for (int i = 0; i < CH / NT; ++i) {
-      const int c = t + NT * i;
-      const int r = c / (BN / 8), c8 = 8 * (c % (BN / 8));
-      *reinterpret_cast<uint4*>(g.out16 + size_t(m0 + r) * g.ldo + n0 + c8) =
-          *reinterpret_cast<const uint4*>(lds + r * LO + c8);
-    }
+  for (int i = 0; i < CH / NT; ++i) {
+    const int c = t + NT * i;
+    const int r = c / (BN / 8), c8 = 8 * (c % (BN / 8));
+    *reinterpret_cast<uint4*>(g.out16 + size_t(m0 + r) * g.ldo + n0 + c8) =
+        *reinterpret_cast<const uint4*>(lds + r * LO + c8);
   }
 }
 
-__global__ __launch_bounds__(512) void k_gemm(GemmArgs g) { gemm_tile<KC>(g, blockIdx.x, blockIdx.y, 0); }
-
-// Weight gradients of several layers in one launch: dW_p = G_p^T X_p over S
-// batch splits, with the column sums of G_p (bias gradients).  Both operands
-// are stored [batch][features] in tiles (row-contiguous in the product's terms);
-// M = width for every problem.  blockIdx.z = problem * S + split; the
-// workgroups of a problem's n tiles beyond its own N leave at once.  Two
-// workgroups of four waves share a compute unit (registers and LDS fit), so
-// a launch of more than one workgroup per compute unit keeps the matrix
-// cores busy while the other workgroup stages.
+// ---- weight gradients -----------------------------------------------------------
+// dW_p = G_p^T X_p of several layers in one launch, over S batch splits, with
+// the column sums of G_p (bias gradients).  M = width for every problem.
+// blockIdx.z = problem * S + split; the workgroups of a problem's n tiles
+// beyond its own N leave at once.
+//
+// A workgroup computes a 128 x 128 tile, a wave a 64 x 64 block of it.  Both
+// operands lie with the batch (the product's k) outermost, in tiles of 32 x
+// 32 (train_layout.h), which go to LDS as they are, by direct copies of 1 KB
+// (the lanes put the samples in order on the way), 32 samples a stage in a
+// ring of four, and are turned into fragments by transposing reads.  Bound by
+// memory: 538 MB at 65,536 rows and 8 layers.  Turning them in registers
+// (8 x 8 byte permutes between a load and an LDS write) took 32 permutes and a
+// write per 64 values beside the products, and the column sums as many again
+// in half of the waves.
+//
+// Two workgroups share a compute unit (64 KB of LDS each), so that one's
+// products cover the other's waits.
 struct WgradProb {
-  const uint16_t* G;  // [B][M]
-  const uint16_t* X;  // [B][ldx], N = padded input width
+  const uint16_t* G;  // [B][M] in tiles
+  const uint16_t* X;  // [B][ldx] in tiles, N = padded input width
   float* part;        // [S][M][N]
   float* colsum;      // [S][M]
   int ldx, N;
@@ -391,6 +267,20 @@ struct WgradBatch {
   WgradProb p[NEDF_TRAIN_MAX_LAYERS];
   int n, S, M, B;
 };
+constexpr int WG_TILE = 128;                  // rows and columns of a workgroup's tile
+constexpr int WG_SLOT = 2 * WG_TILE * 32 * 2;  // bytes of a stage: 32 samples of both operands
+constexpr int WG_SLOTS = 4;
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Of 16 lanes that read 16 values at each of four k (lane l: k l / 4, values
+// 4 (l % 4) ..), lane i gets value i at the four k.
+template <int OFF>
+__device__ __forceinline__ u32x2 lds_read_tr(uint32_t addr) {
+  u32x2 v;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF));
+  return v;
+}
+
 __global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
   // The tiles of one (problem, split) read the same rows of both operands.
   // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin
@@ -405,15 +295,128 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
   const int bx = lid % nx, by = (lid / nx) % ny, bz = lid / (nx * ny);
   const int prob = bz / wb.S, split = bz % wb.S;
   const WgradProb& p = wb.p[prob];
-  if (by * 128 >= p.N) return;  // the whole workgroup
-  GemmArgs g{};
-  g.A = p.G; g.lda = wb.M;
-  g.B = p.X; g.ldb = p.ldx;
-  g.M = wb.M; g.N = p.N; g.K = wb.B;
-  g.k_per_split = wb.B / wb.S;
-  g.part = p.part;
-  g.colsum = p.colsum;
-  gemm_tile<RC>(g, bx, by, split);
+  if (by * WG_TILE >= p.N) return;  // the whole workgroup
+  __shared__ __attribute__((aligned(16))) uint8_t lds[WG_SLOTS * WG_SLOT];
+  __shared__ float s_cs[WG_TILE][8];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
+  const int m0 = bx * WG_TILE, n0 = by * WG_TILE;
+  const int n = wb.B / wb.S / 32;  // stages, a multiple of four
+  // a stage's copies: wave w takes tile w of either operand, in two halves of
+  // 16 samples; sample 8 c + j is row c + 4 j of the tile in memory
+  const size_t a_step = size_t(32) * wb.M, b_step = size_t(32) * p.ldx;
+  const uint16_t* Ab = p.G + size_t(split) * n * a_step + (m0 / 32 + wave) * 1024;
+  const uint16_t* Bb = p.X + size_t(split) * n * b_step + (n0 / 32 + wave) * 1024;
+  const uint32_t copy_off = uint32_t(nedf_train_tile_row(lane >> 2)) * 64u + 16u * (lane & 3);
+  auto copy = [&](int st, int slot) __attribute__((always_inline)) {
+    const int sc = min(st, n - 1);  // the last stage again past the end, into a free slot
+    const eng::gbyte* ga = (const eng::gbyte*)(Ab + sc * a_step);
+    const eng::gbyte* gb = (const eng::gbyte*)(Bb + sc * b_step);
+    uint32_t off = copy_off;
+    asm volatile("" : "+s"(ga), "+s"(gb), "+v"(off));
+    uint8_t* d = lds + slot * WG_SLOT + wave * 2048;
+    __builtin_amdgcn_global_load_lds((const void*)(ga + off), d, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(ga + (off + 128u)), d + 1024, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(gb + off), d + WG_SLOT / 2, 16, 0, 0);
+    __builtin_amdgcn_global_load_lds((const void*)(gb + (off + 128u)), d + WG_SLOT / 2 + 1024, 16, 0, 0);
+  };
+  // fragment reads: lane l takes value l % 32 at samples 8 (l / 32) .. + 7 of
+  // a K-step, in two reads of four samples
+  const uint32_t rd = eng::lds_offset(lds) + uint32_t(8 * (lane >> 5) + ((lane >> 2) & 3)) * 64u +
+                      uint32_t(16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2u;
+  const uint32_t rdA = rd + wm * 4096, rdB = rd + WG_SLOT / 2 + wn * 4096;
+  f32x16_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16_t{};
+  // column sums (the first n tile's workgroups): wave (wm, wn) adds block wn
+  // of its 64 rows; a lane's eight samples of each of four K-steps apart
+  const bool sums = by == 0;
+  float cs[4] = {0.f, 0.f, 0.f, 0.f};
+  copy(0, 0);
+  copy(1, 1);
+  copy(2, 2);
+#pragma unroll 1
+  for (int s0 = 0; s0 < n; s0 += 4) {
+    eng::static_for<4>([&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      // stage s0 + q has landed (the next two may be in flight), and every
+      // wave has read the stage before, whose slot the new copies take
+      eng::dma_wait_barrier_n<8>();
+      copy(s0 + q + 3, (q + 3) % WG_SLOTS);
+      u32x2 f[2][4][2];  // [K-step][A 0, A 1, B 0, B 1][samples 0..3, 4..7]
+      eng::static_for<2>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int ks = decltype(kc)::value;
+        eng::static_for<2>([&](auto ic) __attribute__((always_inline)) {
+          constexpr int i = decltype(ic)::value;
+          constexpr int at = q * WG_SLOT + i * 2048 + ks * 1024;
+          f[ks][i][0] = lds_read_tr<at>(rdA);
+          f[ks][i][1] = lds_read_tr<at + 256>(rdA);
+          f[ks][2 + i][0] = lds_read_tr<at>(rdB);
+          f[ks][2 + i][1] = lds_read_tr<at + 256>(rdB);
+        });
+      });
+      eng::static_for<2>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int ks = decltype(kc)::value;
+        u32x2(&w)[4][2] = f[ks];
+        asm volatile("s_waitcnt lgkmcnt(%8)"
+                     : "+v"(w[0][0]), "+v"(w[0][1]), "+v"(w[1][0]), "+v"(w[1][1]), "+v"(w[2][0]), "+v"(w[2][1]),
+                       "+v"(w[3][0]), "+v"(w[3][1])
+                     : "n"(ks == 0 ? 8 : 0));
+        bf16x8_t o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          o[i] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(w[i][0], w[i][1], 0, 1, 2, 3));
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            // B first: lane l's accumulators hold row m = l % 32 of the block
+            // and, per group of four, four consecutive columns
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o[2 + j], o[i], acc[i][j], 0, 0, 0);
+        if (sums) {
+          float s = 0.f;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const uint32_t v = wn ? w[1][h][e] : w[0][h][e];
+              s += __uint_as_float(v << 16) + __uint_as_float(v & 0xFFFF0000u);
+            }
+          cs[2 * (q & 1) + ks] += s;
+        }
+      });
+    });
+  }
+  // the copies past the end must land before the workgroup gives up its LDS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // accumulator r of block (i, j): row 64 wm + 32 i + lane % 32, column
+  // 64 wn + 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = m0 + wm * 64 + 32 * i + (lane & 31);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int col = n0 + wn * 64 + 32 * j + 8 * q + 4 * (lane >> 5);
+        *reinterpret_cast<float4*>(p.part + (size_t(split) * wb.M + row) * p.N + col) =
+            make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+      }
+  }
+  // the eight sums of a row (sample groups 0..7 of 64) in order
+  if (sums) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s_cs[wm * 64 + 32 * wn + (lane & 31)][2 * k + (lane >> 5)] = cs[k];
+    __syncthreads();
+    if (t < WG_TILE) {
+      float s_ = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s_ += s_cs[t][q];
+      p.colsum[size_t(split) * wb.M + m0 + t] = s_;
+    }
+  }
 }
 
 // Weight and bias gradients of every hidden layer from the split partials,
@@ -630,11 +633,11 @@ __global__ void k_train_encode_points(const float* o_l, const float* d_l, const 
 // Split count of a batched weight-gradient launch over `tiles` 128 x 128
 // output tiles: a power of two up to 64 giving at most 640 workgroups (two
 // per compute unit and a quarter more, so that the last wave of workgroups
-// is short), with the batch a multiple of 128 per split (an even number of
-// 64-deep stages; the batch is a multiple of 256).
+// is short), with the batch a multiple of 128 per split (a whole number of
+// turns of the four-stage ring; the batch is a multiple of 256).
 int wgrad_batch_splits(int B, int tiles) {
   int S = 1;
-  while (S < 64 && tiles * S * 2 <= 640 && B % (S * 2 * 2 * GT_BK) == 0) S *= 2;
+  while (S < 64 && tiles * S * 2 <= 640 && B % (S * 2 * 128) == 0) S *= 2;
   return S;
 }
 
@@ -765,7 +768,7 @@ hipError_t launch_train_step(const nedf_mlp_shape& sh, uint8_t* st, const float*
       maxmn = std::max(maxmn, W * L.Kpad + W);
       ny = std::max(ny, L.Kpad / 128);
     }
-    hipLaunchKernelGGL(k_wgrad, dim3(W / GT_BM, ny, NH * S), dim3(256), 0, s, wb);
+    hipLaunchKernelGGL(k_wgrad, dim3(W / WG_TILE, ny, NH * S), dim3(256), 0, s, wb);
     hipLaunchKernelGGL(k_reduce_grads, dim3(blocks(maxmn), NH + 1), dim3(256), 0, s, ra);
   }
   // Adam on every parameter array, one launch
@@ -892,7 +895,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
       maxmn = std::max(maxmn, W * L.Kpad + W);
       ny = std::max(ny, L.Kpad / 128);
     }
-    hipLaunchKernelGGL(k_wgrad, dim3(W / GT_BM, ny, tl.n_layers * S), dim3(256), 0, s, wb);
+    hipLaunchKernelGGL(k_wgrad, dim3(W / WG_TILE, ny, tl.n_layers * S), dim3(256), 0, s, wb);
     hipLaunchKernelGGL(k_reduce_grads, dim3(blocks(maxmn), tl.n_layers + 1), dim3(256), 0, s, ra);
   }
   // Adam, in launches of at most one argument block of segments
@@ -947,11 +950,10 @@ hipError_t launch_fp8_calibrate(const nedf_mlp_shape& sh, const float* const* W,
     g.B = reinterpret_cast<const uint16_t*>(st + tl.L[l].W16);
     g.ldb = tl.L[l].Kpad;
     g.M = B; g.N = W_; g.K = tl.L[l].Kpad;
-    g.k_per_split = g.K;
     g.bias = reinterpret_cast<const float*>(st + tl.L[l].b);
     g.out16 = Hs + size_t(l) * B * W_;
     g.ldo = W_;
-    hipLaunchKernelGGL(k_gemm, dim3(B / GT_BM, W_ / 256), dim3(512), 0, s, g);
+    hipLaunchKernelGGL(k_gemm, dim3(B / GT_BM, W_ / GT_BN), dim3(512), 0, s, g);
     if (l + 1 < NH) hipLaunchKernelGGL(k_amax16, dim3(256), dim3(256), 0, s, g.out16, size_t(B) * W_, amax + NEDF_MAX_LAYERS + l + 1);
     hipLaunchKernelGGL(k_amax32, dim3(64), dim3(256), 0, s, reinterpret_cast<const float*>(st + tl.L[l].W),
                        size_t(tl.L[l].N) * tl.L[l].K, amax + l);
