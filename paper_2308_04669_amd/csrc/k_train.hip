@@ -241,21 +241,19 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs g) {
 // ---- weight gradients -----------------------------------------------------------
 // dW_p = G_p^T X_p of several layers in one launch, over S batch splits, with
 // the column sums of G_p (bias gradients).  M = width for every problem.
-// blockIdx.z = problem * S + split; the workgroups of a problem's n tiles
-// beyond its own N leave at once.
 //
 // A workgroup computes a 128 x 128 tile, a wave a 64 x 64 block of it.  Both
 // operands lie with the batch (the product's k) outermost, in tiles of 32 x
 // 32 (train_layout.h), which go to LDS as they are, by direct copies of 1 KB
 // (the lanes put the samples in order on the way), 32 samples a stage in a
-// ring of four, and are turned into fragments by transposing reads.  Bound by
+// ring of three, and are turned into fragments by transposing reads.  Bound by
 // memory: 538 MB at 65,536 rows and 8 layers.  Turning them in registers
 // (8 x 8 byte permutes between a load and an LDS write) took 32 permutes and a
 // write per 64 values beside the products, and the column sums as many again
 // in half of the waves.
 //
-// Two workgroups share a compute unit (64 KB of LDS each), so that one's
-// products cover the other's waits.
+// Three workgroups share a compute unit (48 KB of LDS each), so that the
+// others' products cover one's waits, and a launch of up to 768 is one round.
 struct WgradProb {
   const uint16_t* G;  // [B][M] in tiles
   const uint16_t* X;  // [B][ldx] in tiles, N = padded input width
@@ -269,7 +267,7 @@ struct WgradBatch {
 };
 constexpr int WG_TILE = 128;                  // rows and columns of a workgroup's tile
 constexpr int WG_SLOT = 2 * WG_TILE * 32 * 2;  // bytes of a stage: 32 samples of both operands
-constexpr int WG_SLOTS = 4;
+constexpr int WG_SLOTS = 3;
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // Of 16 lanes that read 16 values at each of four k (lane l: k l / 4, values
@@ -281,27 +279,27 @@ __device__ __forceinline__ u32x2 lds_read_tr(uint32_t addr) {
   return v;
 }
 
-__global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
+__global__ __launch_bounds__(256, 3) void k_wgrad(WgradBatch wb) {
   // The tiles of one (problem, split) read the same rows of both operands.
-  // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin
-  // by linear id, so logical workgroup l = (id % 8) * (total / 8) + id / 8
-  // (a bijection when total is a multiple of 8) puts consecutive logical
-  // ids, and with them a slice's tiles, on one XCD: the second read of each
-  // operand row is an L2 hit instead of an HBM read.
-  const int nx = gridDim.x, ny = gridDim.y;
-  const int total = nx * ny * int(gridDim.z);
-  const int id = int(blockIdx.x) + nx * (int(blockIdx.y) + ny * int(blockIdx.z));
-  const int lid = total % 8 == 0 ? (id % 8) * (total / 8) + id / 8 : id;
-  const int bx = lid % nx, by = (lid / nx) % ny, bz = lid / (nx * ny);
-  const int prob = bz / wb.S, split = bz % wb.S;
+  // Workgroups are handed to the 8 XCDs (each with its own L2) round-robin, so
+  // consecutive logical ids lie on one XCD, an eighth of them on each: the
+  // second read of an operand row is an L2 hit instead of an HBM read.  (A
+  // grid over the widest problem's tiles, whose other workgroups left at
+  // once, gave the XCD with the classifier's head 1.7 times the others' work.)
+  const int total = gridDim.x, xcd = blockIdx.x % 8;
+  const int lid = xcd * (total / 8) + min(xcd, total % 8) + int(blockIdx.x) / 8;
+  // problem 0 has an input width of its own, the others N = M
+  const int nx = wb.M / WG_TILE, t0 = nx * (wb.p[0].N / WG_TILE), t1 = nx * nx;
+  const int rest = lid - t0 * wb.S;
+  const int prob = rest < 0 ? 0 : 1 + rest / (t1 * wb.S);
+  const int at = rest < 0 ? lid : rest % (t1 * wb.S), tiles = rest < 0 ? t0 : t1;
+  const int split = at / tiles, bx = (at % tiles) % nx, by = (at % tiles) / nx;
   const WgradProb& p = wb.p[prob];
-  if (by * WG_TILE >= p.N) return;  // the whole workgroup
   __shared__ __attribute__((aligned(16))) uint8_t lds[WG_SLOTS * WG_SLOT];
-  __shared__ float s_cs[WG_TILE][8];
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave >> 1, wn = wave & 1;
   const int m0 = bx * WG_TILE, n0 = by * WG_TILE;
-  const int n = wb.B / wb.S / 32;  // stages, a multiple of four
+  const int n = wb.B / wb.S / 32;  // stages, an even number
   // a stage's copies: wave w takes tile w of either operand, in two halves of
   // 16 samples; sample 8 c + j is row c + 4 j of the tile in memory
   const size_t a_step = size_t(32) * wb.M, b_step = size_t(32) * p.ldx;
@@ -336,25 +334,27 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
   float cs[4] = {0.f, 0.f, 0.f, 0.f};
   copy(0, 0);
   copy(1, 1);
-  copy(2, 2);
+  int cur = 0;
 #pragma unroll 1
-  for (int s0 = 0; s0 < n; s0 += 4) {
-    eng::static_for<4>([&](auto qc) __attribute__((always_inline)) {
+  for (int s0 = 0; s0 < n; s0 += 2) {
+    eng::static_for<2>([&](auto qc) __attribute__((always_inline)) {
       constexpr int q = decltype(qc)::value;
-      // stage s0 + q has landed (the next two may be in flight), and every
+      // stage s0 + q has landed (the next one may be in flight), and every
       // wave has read the stage before, whose slot the new copies take
-      eng::dma_wait_barrier_n<8>();
-      copy(s0 + q + 3, (q + 3) % WG_SLOTS);
+      eng::dma_wait_barrier_n<4>();
+      copy(s0 + q + 2, cur == 0 ? 2 : cur - 1);
+      const uint32_t atA = rdA + cur * WG_SLOT, atB = rdB + cur * WG_SLOT;
+      cur = cur == 2 ? 0 : cur + 1;
       u32x2 f[2][4][2];  // [K-step][A 0, A 1, B 0, B 1][samples 0..3, 4..7]
       eng::static_for<2>([&](auto kc) __attribute__((always_inline)) {
         constexpr int ks = decltype(kc)::value;
         eng::static_for<2>([&](auto ic) __attribute__((always_inline)) {
           constexpr int i = decltype(ic)::value;
-          constexpr int at = q * WG_SLOT + i * 2048 + ks * 1024;
-          f[ks][i][0] = lds_read_tr<at>(rdA);
-          f[ks][i][1] = lds_read_tr<at + 256>(rdA);
-          f[ks][2 + i][0] = lds_read_tr<at>(rdB);
-          f[ks][2 + i][1] = lds_read_tr<at + 256>(rdB);
+          constexpr int at = i * 2048 + ks * 1024;
+          f[ks][i][0] = lds_read_tr<at>(atA);
+          f[ks][i][1] = lds_read_tr<at + 256>(atA);
+          f[ks][2 + i][0] = lds_read_tr<at>(atB);
+          f[ks][2 + i][1] = lds_read_tr<at + 256>(atB);
         });
       });
       eng::static_for<2>([&](auto kc) __attribute__((always_inline)) {
@@ -384,7 +384,7 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
               const uint32_t v = wn ? w[1][h][e] : w[0][h][e];
               s += __uint_as_float(v << 16) + __uint_as_float(v & 0xFFFF0000u);
             }
-          cs[2 * (q & 1) + ks] += s;
+          cs[2 * q + ks] += s;
         }
       });
     });
@@ -407,6 +407,8 @@ __global__ __launch_bounds__(256, 2) void k_wgrad(WgradBatch wb) {
   }
   // the eight sums of a row (sample groups 0..7 of 64) in order
   if (sums) {
+    float(&s_cs)[WG_TILE][8] = *reinterpret_cast<float(*)[WG_TILE][8]>(lds);
+    __syncthreads();  // the ring is free
 #pragma unroll
     for (int k = 0; k < 4; ++k) s_cs[wm * 64 + 32 * wn + (lane & 31)][2 * k + (lane >> 5)] = cs[k];
     __syncthreads();
@@ -633,8 +635,8 @@ __global__ void k_train_encode_points(const float* o_l, const float* d_l, const 
 // Split count of a batched weight-gradient launch over `tiles` 128 x 128
 // output tiles: a power of two up to 64 giving at most 640 workgroups (two
 // per compute unit and a quarter more, so that the last wave of workgroups
-// is short), with the batch a multiple of 128 per split (a whole number of
-// turns of the four-stage ring; the batch is a multiple of 256).
+// is short), with the batch a multiple of 128 per split (the batch is a
+// multiple of 256).
 int wgrad_batch_splits(int B, int tiles) {
   int S = 1;
   while (S < 64 && tiles * S * 2 <= 640 && B % (S * 2 * 128) == 0) S *= 2;
@@ -759,16 +761,15 @@ hipError_t launch_train_step(const nedf_mlp_shape& sh, uint8_t* st, const float*
     ra.step = reinterpret_cast<int64_t*>(st);
     ra.hpart = hpart; ra.h_blocks = hblocks;
     ra.gWh = F(hd.gW); ra.gbh = F(hd.gb); ra.loss = loss;
-    int maxmn = 517 * 64, ny = 1;  // the head slice: one wave per output
+    int maxmn = 517 * 64;  // the head slice: one wave per output
     for (int l = 0; l < NH; ++l) {
       const nedf_train_layer& L = tl.L[l];
       wb.p[l] = WgradProb{Gl(l), l == 0 ? Hin : Hl(l - 1), wpart[l], wpart[l] + size_t(S) * W * L.Kpad,
                           l == 0 ? K0p : W, L.Kpad};
       ra.L[l] = ReduceLayer{wb.p[l].part, wb.p[l].colsum, F(L.gW), F(L.gb), W, L.Kpad, L.K};
       maxmn = std::max(maxmn, W * L.Kpad + W);
-      ny = std::max(ny, L.Kpad / 128);
     }
-    hipLaunchKernelGGL(k_wgrad, dim3(W / WG_TILE, ny, NH * S), dim3(256), 0, s, wb);
+    hipLaunchKernelGGL(k_wgrad, dim3(regression_wgrad_tiles(sh, tl) * S), dim3(256), 0, s, wb);
     hipLaunchKernelGGL(k_reduce_grads, dim3(blocks(maxmn), NH + 1), dim3(256), 0, s, ra);
   }
   // Adam on every parameter array, one launch
@@ -885,7 +886,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
     ra.step = reinterpret_cast<int64_t*>(st);
     ra.hpart = w.lpart; ra.h_blocks = B / 128; ra.B = B;
     ra.loss = loss;
-    int maxmn = 0, ny = 1;
+    int maxmn = 0;
     for (int i = 0; i < tl.n_layers; ++i) {
       const nedf_train_layer& L = tl.L[i];
       const uint16_t* X = i == 0 ? w.X : i == tail ? Hk(NB) : (i % 2 == 1 ? Hk((i - 1) / 2) : Ak((i - 2) / 2));
@@ -893,9 +894,8 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
       wb.p[i] = WgradProb{Gi(i), X, part, part + size_t(S) * W * L.Kpad, i == 0 ? K0p : W, L.Kpad};
       ra.L[i] = ReduceLayer{part, part + size_t(S) * W * L.Kpad, F(L.gW), F(L.gb), W, L.Kpad, L.K};
       maxmn = std::max(maxmn, W * L.Kpad + W);
-      ny = std::max(ny, L.Kpad / 128);
     }
-    hipLaunchKernelGGL(k_wgrad, dim3(W / WG_TILE, ny, tl.n_layers * S), dim3(256), 0, s, wb);
+    hipLaunchKernelGGL(k_wgrad, dim3(cls_wgrad_tiles(tl, W) * S), dim3(256), 0, s, wb);
     hipLaunchKernelGGL(k_reduce_grads, dim3(blocks(maxmn), tl.n_layers + 1), dim3(256), 0, s, ra);
   }
   // Adam, in launches of at most one argument block of segments
