@@ -12,7 +12,6 @@
 namespace nedf {
 namespace {
 
-using chain::gload1;
 using chain::kstep_off;
 using chain::gstore;
 using chain::gstore1;
@@ -47,6 +46,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
   __shared__ __attribute__((aligned(16))) float s_bias[NEDF_MAX_LAYERS * 256];
   __shared__ __attribute__((aligned(16))) float s_head[2 * 256];
   __shared__ __attribute__((aligned(16))) float s_red[NW * 512];
+  __shared__ __attribute__((aligned(16))) uint8_t s_bits[2 * NW * 1024];
   __shared__ __attribute__((aligned(16))) float s_row[4][32 * NW];
   __shared__ float s_label[2][32 * NW];
   constexpr int NT = 64 * NW;
@@ -160,18 +160,25 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
     bf16x8_t B0[K0];
 #pragma unroll
     for (int i = 0; i < K0; ++i) B0[i] = __builtin_bit_cast(bf16x8_t, B0u[i]);
-    chain::layer<K0, 8, 16, NW, true, 2, 0>(B0, a.w[0], NH > 1 ? a.w[1] : nullptr, lds, cur, bias0, fwd_store(0));
+    chain::layer<K0, 8, 16, NW, true, 2, 0, 0>(B0, a.w[0], NH > 1 ? a.w[1] : nullptr, lds, cur, bias0, fwd_store(0));
     advance();
   }
   for (int l = 1; l + 1 < NH; ++l) {
-    chain::layer<16, 8, 16, NW, true, 2, 2>(X, a.w[l], a.w[l + 1], lds, cur, bias0 + l * 1024, fwd_store(l));
+    chain::layer<16, 8, 16, NW, true, 2, 2, 2>(X, a.w[l], a.w[l + 1], lds, cur, bias0 + l * 1024, fwd_store(l));
     advance();
   }
   if (NH > 1) {
     // backward weights follow in the ring
-    chain::layer<16, 8, 16, NW, true, 0, 2>(X, a.w[NH - 1], a.wt[NH - 1], lds, cur, bias0 + (NH - 1) * 1024, fwd_last);
+    chain::layer<16, 8, 16, NW, true, 0, 2, 2>(X, a.w[NH - 1], a.wt[NH - 1], lds, cur, bias0 + (NH - 1) * 1024, fwd_last);
     advance();
   }
+  // signs of H_{l-1}, copied a layer ahead, into two places by turns
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  auto bits_at = [&](int l) __attribute__((always_inline)) { return s_bits + ((l & 1) * NW + uwave) * 1024; };
+  auto fetch_bits = [&](int l) __attribute__((always_inline)) {
+    chain::copy_bits(bits0 + size_t(l) * layer_bits + uwave * 1024, bits_at(l));
+  };
+  if (NH > 1) fetch_bits(NH - 2);
   // ---- head and loss.  The two dot products take a row's features in order
   // in four quarters, (q0 + q1) + (q2 + q3); a quarter's groups of eight
   // features alternate between the lane halves.
@@ -298,6 +305,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
   // unpacked from the dot products on, they spilled)
 #pragma unroll
   for (int ks = 0; ks < 16; ++ks) asm volatile("" : "+v"(X[ks]));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the first signs have landed
   {
     const float4* hw = reinterpret_cast<const float4*>(s_head);
     uint16_t* dst = G0 + size_t(NH - 1) * layer_elems;
@@ -324,10 +332,9 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
   }
   // ---- data gradients: G_{l-1} = (G_l W_l) * (H_{l-1} > 0)
   for (int l = NH - 1; l > 0; --l) {
-    // the signs of H_{l-1}; in flight over the first superchunk's reads
     uint32_t mb[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) mb[i] = gload1(bits0 + size_t(l - 1) * layer_bits, bit_off + 256 * i);
+    chain::read_bits(mb, bits_at(l - 1));
+    if (l > 1) fetch_bits(l - 2);
     uint16_t* dst = G0 + size_t(l - 1) * layer_elems;
     auto bwd = [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
 #pragma unroll
@@ -340,31 +347,36 @@ __global__ __launch_bounds__(64 * NW, 1) void k_chain_line(ChainLineArgs a) {
         gstore(dst, row_off + kstep_off(2 * fb + q / 2), k);
       }
     };
-    // the first of these layers follows 16 stores of G, the others a layer's
-    chain::layer<16, 8, 16, NW, false, 2, 2>(X, a.wt[l], l > 1 ? a.wt[l - 1] : nullptr, lds, cur, 0u, bwd);
+    // the first of these layers follows 16 stores of G, the others a layer's six
+    chain::layer<16, 8, 16, NW, false, 2, 2, 2>(X, a.wt[l], l > 1 ? a.wt[l - 1] : nullptr, lds, cur, 0u, bwd);
     advance();
   }
 }
 
 // Classifier form: the head (K outermost), the residual blocks, the tail with
 // its loss (Eq. 6), and the data gradients with the skip path's float32
-// gradient, of a workgroup's 128 rows (a wave's residual stream, skip gradient
-// and two operands take more registers than two waves per SIMD leave).
+// gradient, of a workgroup's 32 NW rows (a wave's residual stream, skip
+// gradient and two operands take more registers than two waves per SIMD
+// leave).
 //
-// Bound by the matrix cores of one wave per SIMD and, in large batches, by the
-// writes of the 67 arrays of B x 256 values that the weight gradients read.
-// With it the step of 16 blocks takes 810 us at 16,384 rows against 1,519 us
-// with a launch per layer and direction (and the float32 gradient stream in
-// memory).
+// Bound by one wave's own instruction stream up to a round of workgroups (350
+// us for 16 blocks from 256 rows on, 415 us at 16,384: about 1,000
+// instructions beside the 128 matrix ops of a layer and nobody else on the
+// SIMD), beyond it by the writes of the 67 arrays of B x 256 values that the
+// weight gradients read.  With it the step takes 685 us at 16,384 rows
+// against 1,519 us with a launch per layer and direction (and the float32
+// gradient stream in memory).
 constexpr int CLS_OUT = 1 + NEDF_CLS_COARSE + NEDF_CLS_FINE;
 __device__ __forceinline__ float softplus_f(float z) { return fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))); }
 
-__global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
-  constexpr int NW = 4, K0 = 64;  // waves; K-steps of the encoded input
+template <int NW>
+__global__ __launch_bounds__(64 * NW, 1) void k_chain_points(ChainPointsArgs a) {
+  constexpr int K0 = 64;  // K-steps of the encoded input
   constexpr int NI = eng::dma_instr(chain::SLOT, NW);
   __shared__ __attribute__((aligned(16))) uint8_t lds[chain::RING];
   __shared__ __attribute__((aligned(16))) float s_bias[NEDF_TRAIN_MAX_LAYERS * 256];
   __shared__ float s_red[NW][2];
+  __shared__ __attribute__((aligned(16))) uint8_t s_bits[2 * NW * 1024];
   const int t = threadIdx.x, lane = t & 63, half = lane >> 5, wave = t >> 6;
   const int NB = a.n_blocks, tail = 2 * NB + 1;
   const uint32_t tile_off = chain::tile_off(lane);
@@ -462,7 +474,7 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
     const int i1 = 1 + 2 * k, i2 = i1 + 1;
     uint16_t* Ak = A0 + k * elems;
     uint8_t* ba = bits0 + size_t(i1) * lbits;
-    chain::layer<16, 8, 16, NW, true, 2, 2>(
+    chain::layer<16, 8, 16, NW, true, 2, 2, 2>(
         X, a.w[i1], a.w[i2], lds, cur, bias0 + i1 * 1024, [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
@@ -480,7 +492,7 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
         });
     uint16_t* Hn = H0 + (k + 1) * elems;
     uint8_t* br = bits0 + size_t(i2) * lbits;
-    chain::layer<16, 8, 16, NW, true, 2, 2>(
+    chain::layer<16, 8, 16, NW, true, 2, 2, 2>(
         Y, a.w[i2], a.w[i2 + 1], lds, cur, bias0 + i2 * 1024,
         [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
 #pragma unroll
@@ -500,6 +512,15 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
           if ((fb & 1) && q == 3) gstore1(br, bit_off + 256 * (fb / 2), bits);
         });
   }
+  // signs, copied a layer ahead, into two places by turns; the layers take the
+  // arrays from the last one down
+  uint32_t mb[4];
+  const int uwave = __builtin_amdgcn_readfirstlane(wave);
+  auto bits_at = [&](int i) __attribute__((always_inline)) { return s_bits + ((i & 1) * NW + uwave) * 1024; };
+  auto fetch_bits = [&](int i) __attribute__((always_inline)) {
+    chain::copy_bits(bits0 + size_t(i) * lbits + uwave * 1024, bits_at(i));
+  };
+  fetch_bits(2 * NB);
   // ---- tail and loss: target bins from S of mu*; binary cross-entropy with
   // logits, bins averaged per level and counted for hits only
   {
@@ -514,7 +535,7 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
     uint16_t* Gt = G0 + size_t(tail) * elems;
     // the logits first: the loss's exponentials and logarithms need more
     // registers than a layer's reads in flight leave
-    chain::layer<16, 8, 16, NW, true, 0, 2>(
+    chain::layer<16, 8, 16, NW, true, 0, 2, 2>(
         X, a.w[tail], a.wt[tail], lds, cur, bias0 + tail * 1024,
         [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
 #pragma unroll
@@ -566,19 +587,18 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
   }
   __syncthreads();
   if (t == 0) {
-    const float lb = (s_red[0][0] + s_red[1][0]) + (s_red[2][0] + s_red[3][0]);
-    const float lh = (s_red[0][1] + s_red[1][1]) + (s_red[2][1] + s_red[3][1]);
+    float lb = 0.f, lh = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; w += 2) {
+      lb += s_red[w][0] + s_red[w + 1][0];
+      lh += s_red[w][1] + s_red[w + 1][1];
+    }
     float* P = a.lpart + size_t(blockIdx.x) * 3;
     P[0] = lb + a.w_hit * lh;
     P[1] = lb;
     P[2] = lh;
   }
   // ---- data gradients
-  uint32_t mb[4];
-  auto load_bits = [&](int i) __attribute__((always_inline)) {
-#pragma unroll
-    for (int w = 0; w < 4; ++w) mb[w] = gload1(bits0 + size_t(i) * lbits, bit_off + 256 * w);
-  };
   // a masked quarter of a block into `out` and the gradient array `dst`
   auto masked = [&](bf16x8_t(&out)[16], uint16_t* dst, int fb, int q, const float (&v)[4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -591,9 +611,10 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
     }
   };
   {
-    load_bits(2 * NB);
+    chain::read_bits(mb, bits_at(2 * NB));
+    fetch_bits(2 * NB - 1);
     uint16_t* dst = G0 + size_t(2 * NB) * elems;
-    chain::layer<16, 8, 16, NW, false, 2, 2>(
+    chain::layer<16, 8, 16, NW, false, 2, 2, 2>(
         Y, a.wt[tail], a.wt[2 * NB], lds, cur, 0u, [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
           float o[4];
 #pragma unroll
@@ -603,17 +624,19 @@ __global__ __launch_bounds__(256, 1) void k_chain_points(ChainPointsArgs a) {
   }
   for (int k = NB - 1; k >= 0; --k) {
     const int i1 = 1 + 2 * k, i2 = i1 + 1;
-    load_bits(i1);
+    chain::read_bits(mb, bits_at(i1));
+    fetch_bits(i1 - 1);
     uint16_t* d1 = G0 + size_t(i1) * elems;
-    chain::layer<16, 8, 16, NW, false, 2, 2>(
+    chain::layer<16, 8, 16, NW, false, 2, 2, 2>(
         X, a.wt[i2], a.wt[i1], lds, cur, 0u, [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
           const float o[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
           masked(Y, d1, fb, q, o);
         });
     // masked by the second layer of the block before, or by the head's output
-    load_bits(i1 - 1);
+    chain::read_bits(mb, bits_at(i1 - 1));
+    if (k > 0) fetch_bits(i1 - 2);
     uint16_t* d0 = G0 + size_t(i1 - 1) * elems;
-    chain::layer<16, 8, 16, NW, false, 2, 2>(
+    chain::layer<16, 8, 16, NW, false, 2, 2, 2>(
         Y, a.wt[i1], k > 0 ? a.wt[i1 - 1] : nullptr, lds, cur, 0u,
         [&](int fb, int q, const f32x16_t& v) __attribute__((always_inline)) {
           float o[4];
@@ -639,6 +662,11 @@ int chain_line_waves(int B, int cus) {
   return 9 * r8 <= 5 * r4 ? 8 : 4;
 }
 
+int chain_points_waves(int B, int cus) {
+  const int r2 = (B / 64 + cus - 1) / cus, r4 = (B / 128 + cus - 1) / cus;
+  return r2 <= r4 ? 2 : 4;
+}
+
 void launch_chain_line(const ChainLineArgs& a, int n_comp, int k0, int waves, hipStream_t s) {
   if (n_comp == 6) {
     if (waves == 8) launch_line<6, 8>(a, k0, s);
@@ -649,8 +677,9 @@ void launch_chain_line(const ChainLineArgs& a, int n_comp, int k0, int waves, hi
   }
 }
 
-void launch_chain_points(const ChainPointsArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_chain_points, dim3(a.B / 128), dim3(256), 0, s, a);
+void launch_chain_points(const ChainPointsArgs& a, int waves, hipStream_t s) {
+  if (waves == 2) hipLaunchKernelGGL((k_chain_points<2>), dim3(a.B / 64), dim3(128), 0, s, a);
+  else hipLaunchKernelGGL((k_chain_points<4>), dim3(a.B / 128), dim3(256), 0, s, a);
 }
 
 }  // namespace nedf

@@ -834,7 +834,7 @@ ClsTrainWs cls_train_ws(const nedf_mlp_shape& sh, int B, uint8_t* base) {
     nf = (nf + 63) & ~size_t(63);
   }
   w.wpart = reinterpret_cast<float*>(take(nf * 4));
-  w.lpart = reinterpret_cast<float*>(take(size_t(B / 128) * 3 * 4));
+  w.lpart = reinterpret_cast<float*>(take(size_t(B / 64) * 3 * 4));
   w.end = off;
   return w;
 }
@@ -859,6 +859,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
   auto Ak = [&](int k) { return w.A + size_t(k) * B * W; };
   auto Gi = [&](int i) { return w.G + size_t(i) * B * W; };  // gradient at layer i's pre-activation
   const int tail = tl.n_layers - 1;
+  const int waves = chain_points_waves(B, cu_count());
   prof_mark("train.step", s, true);
   // gamma_10 (the only classifier encoding training accepts)
   hipLaunchKernelGGL(k_train_encode_points<10>, dim3(blocks(size_t(B) * (K0p / 8))), dim3(256), 0, s, o_l, d_l, depth,
@@ -873,7 +874,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
     }
     c.X = w.X; c.mu = w.mu; c.alpha = w.alpha;
     c.H = w.H; c.A = w.A; c.G = w.G; c.bits = w.bits; c.lpart = w.lpart;
-    launch_chain_points(c, s);
+    launch_chain_points(c, waves, s);
   }
   // weight gradients of every layer from its pre-activation gradient and its
   // input, in one launch, then their sums over the splits in order
@@ -884,7 +885,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
     ra.n_layers = tl.n_layers;
     ra.S = S;
     ra.step = reinterpret_cast<int64_t*>(st);
-    ra.hpart = w.lpart; ra.h_blocks = B / 128; ra.B = B;
+    ra.hpart = w.lpart; ra.h_blocks = B / (32 * waves); ra.B = B;
     ra.loss = loss;
     int maxmn = 0;
     for (int i = 0; i < tl.n_layers; ++i) {

@@ -31,7 +31,6 @@ typedef __attribute__((address_space(1))) char gbyte;
 __device__ __forceinline__ void gstore(void* base, uint32_t off, u32x4 v) { *(gvec*)((gbyte*)base + off) = v; }
 __device__ __forceinline__ void gstore1(void* base, uint32_t off, uint32_t v) { *(gword*)((gbyte*)base + off) = v; }
 __device__ __forceinline__ u32x4 gload(const void* base, uint32_t off) { return *(gvec*)((gbyte*)base + off); }
-__device__ __forceinline__ uint32_t gload1(const void* base, uint32_t off) { return *(gword*)((gbyte*)base + off); }
 
 // The arrays kept for the weight gradients are stored in tiles of 32 rows x
 // 32 features, [row block][feature block][row][feature]: a K-step's store
@@ -67,16 +66,17 @@ __device__ __forceinline__ void prime(const uint8_t* w, uint8_t* lds, int cur) {
 // superchunk 1 on its way.
 //
 // epi stores ST times (0 or 2: after quarters 1 and 3) to global memory per
-// block; the previous layer stored SP times after its last barrier.  The wait
-// at the end of superchunk sc is for the copies of superchunk sc + 1, issued
-// before the barrier at the end of sc - 1.  Vector-memory operations retire
-// in order, so it may leave in flight whatever was certainly issued after
-// that barrier (the compiler may move stores past copies, not past barriers):
-// the copies of superchunk sc + 2 and the stores made in superchunk sc, which
-// are the second one of block 2 sc - 2, both of block 2 sc - 1 and the first
-// one of block 2 sc (in a layer's first superchunk: the previous layer's last
-// block's, and block 0's first if its quarter 1 comes before the barrier).
-template <int K0, int FB, int KN, int NW, bool BIAS, int ST, int SP, class EPI>
+// block; the previous layer's PST times, SP stores of it lying after its last
+// barrier.  The wait at the end of superchunk sc is for the copies of
+// superchunk sc + 1.  Vector-memory operations retire in order, and a store
+// takes about as long as a superchunk, so the wait leaves in flight all that
+// was certainly issued after those copies (at the start of superchunk sc - 1,
+// with the compiler kept from moving memory operations past them): the copies
+// of superchunk sc + 2 and the stores of two superchunks.  A superchunk's
+// last read group is consumed after its barrier, so that before the barrier
+// lie PRE of its ST SB stores, both of the block before it and, with four
+// read groups or more to a block, the first one of its own first block.
+template <int K0, int FB, int KN, int NW, bool BIAS, int ST, int PST, int SP, class EPI>
 __device__ __forceinline__ void layer(const bf16x8_t (&Bin)[K0], const uint8_t* w, const uint8_t* w_next, uint8_t* lds,
                                       int& cur, uint32_t bias_addr, EPI&& epi) {
   constexpr int NSC = FB / SB;
@@ -170,7 +170,8 @@ __device__ __forceinline__ void layer(const bf16x8_t (&Bin)[K0], const uint8_t* 
     uint8_t* nbuf = lds + next_slot(next_slot(cur)) * SLOT;
     constexpr bool own = sc + 2 < NSC;
     constexpr int NI = own ? eng::dma_instr(SCB, NW) : eng::dma_instr(SCN, NW);
-    constexpr int young = sc == 0 ? SP + (NG >= 4 ? ST / 2 : 0) : 2 * ST;
+    constexpr int OWN = NG >= 4 ? ST / 2 : 0, PRE = ST + OWN;
+    constexpr int young = sc == 0 ? SB * PST + SP + OWN : sc == 1 ? OWN + (SB * ST - PRE) + PRE : SB * ST + PRE;
     bool issued = own;
     if constexpr (own) {
       eng::dma_chunk<SCB, NW>(w + size_t(sc + 2) * SCB, nbuf);
@@ -178,6 +179,7 @@ __device__ __forceinline__ void layer(const bf16x8_t (&Bin)[K0], const uint8_t* 
       eng::dma_chunk<SCN, NW>(w_next + size_t(sc + 2 - NSC) * SCN, nbuf);
       issued = true;
     }
+    asm volatile("" ::: "memory");
     auto pass_barrier = [&]() __attribute__((always_inline)) {
       if (issued) eng::dma_wait_barrier_n<NI + young>();
       else eng::dma_wait_barrier();
@@ -223,6 +225,27 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2_t;
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
   const f32x2_t f = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
+}
+
+// A wave's sign words of a layer, [block pair][lane], copied to its 1 KB of
+// LDS a layer ahead and read there.  (As loads to registers they made the
+// compiler drain every store and copy in flight, once per layer.)  The copy
+// has landed once the wave has passed the barriers of a layer begun after it.
+__device__ __forceinline__ void copy_bits(const uint8_t* src, uint8_t* dst) {
+  const eng::gbyte* base = (const eng::gbyte*)src;
+  uint32_t off = (threadIdx.x & 63) * 16u;
+  asm volatile("" : "+s"(base), "+v"(off));
+  __builtin_amdgcn_global_load_lds((const void*)(base + off), dst, 16, 0, 0);
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void read_bits(uint32_t (&m)[4], const uint8_t* src) {
+  const uint32_t at = eng::lds_offset(src) + (threadIdx.x & 63) * 4u;
+  asm volatile(
+      "ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:256\n\tds_read_b32 %2, %4 offset:512\n\t"
+      "ds_read_b32 %3, %4 offset:768\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(m[0]), "=&v"(m[1]), "=&v"(m[2]), "=&v"(m[3])
+      : "v"(at)
+      : "memory");
 }
 
 // Half of a block's packed words (accumulator order, two features each) as

@@ -38,7 +38,7 @@ struct ChainPointsArgs {
   uint16_t *H, *A;                           // [n_blocks + 1][B][256] stream, [n_blocks][B][256] inner activations
   uint16_t* G;                               // [layers][B][256] gradients at the pre-activations
   uint8_t* bits;                             // [2 n_blocks + 1] sign arrays as in ChainLineArgs
-  float* lpart;                              // [B / 128][3] loss sums (total, bins, hit)
+  float* lpart;                              // [workgroups][3] loss sums (total, bins, hit)
 };
 
 // Waves per workgroup (each 32 rows) for a batch of B rows on `cus` compute
@@ -46,7 +46,12 @@ struct ChainPointsArgs {
 // ones and holds twice the rows.
 int chain_line_waves(int B, int cus);
 void launch_chain_line(const ChainLineArgs& a, int n_comp, int k0, int waves, hipStream_t s);
-void launch_chain_points(const ChainPointsArgs& a, hipStream_t s);
+// Two waves per workgroup while that is no more rounds than four (the chain
+// of 16 blocks: 421 against 432 us at 16,384 rows, where four waves leave
+// half of the compute units empty; 584 us with four at 32,768 rows, two
+// rounds of 415 with two).
+int chain_points_waves(int B, int cus);
+void launch_chain_points(const ChainPointsArgs& a, int waves, hipStream_t s);
 
 int cu_count();
 

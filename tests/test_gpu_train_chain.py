@@ -67,7 +67,7 @@ def test_line_chain(in_kind, enc_L, depth, B, monkeypatch):
                                              hit.astype(np.float64), gemm="bf16"))
 
 
-@pytest.mark.parametrize("n_blocks,B", [(1, 256), (2, 768)])
+@pytest.mark.parametrize("n_blocks,B", [(1, 256), (2, 768), (1, 16640)])  # two waves; four past one round of them
 def test_points_chain(n_blocks, B):
     need_gpu()
     log(f"case: classifier, {n_blocks} blocks, B = {B}")
