@@ -381,30 +381,14 @@ __device__ __forceinline__ void push_slab(const KArgs& a, int32_t* cnt, int lane
   }
 }
 
-// Tests the pairs whose bits are set in `hits` (lane's pairs q0 + j) against
-// the pixels' current nearest hits and appends the survivors to list S.  The
-// wave first compacts the candidate indices in LDS (`cand`, 1024 entries) and
-// then takes them 64 * SLAB_U at a time, SLAB_U per lane, so that the bound,
-// pair and key reads of all of them are in flight together.  Called with the
-// whole wave active.
-__device__ __forceinline__ void slab_candidates(const KArgs& a, int32_t* cnt, int* cand, int lane, int q0,
-                                                uint32_t hits) {
-  const int c = __popc(hits);
-  int incl = c;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(incl, off);
-    if (lane >= off) incl += y;
-  }
-  const int n_cand = __shfl(incl, 63);
-  if (n_cand == 0) return;
-  int k = incl - c;
-  while (hits) {
-    cand[k++] = q0 + __ffs(hits) - 1;
-    hits &= hits - 1u;
-  }
+// Tests the n pairs whose indices the wave has gathered in LDS (`cand`)
+// against the pixels' current nearest hits and appends the survivors to list
+// S, 64 * SLAB_U at a time, SLAB_U per lane, so that the bound, pair and key
+// reads of all of them are in flight together.  Called with the whole wave
+// active.
+__device__ __forceinline__ void slab_test(const KArgs& a, int32_t* cnt, const int* cand, int lane, int n) {
   __builtin_amdgcn_wave_barrier();
-  for (int c0 = 0; c0 < n_cand; c0 += 64 * SLAB_U) {
+  for (int c0 = 0; c0 < n; c0 += 64 * SLAB_U) {
     bool keep[SLAB_U];
     int q[SLAB_U], m[SLAB_U];
     uint2 pr[SLAB_U];
@@ -414,7 +398,7 @@ __device__ __forceinline__ void slab_candidates(const KArgs& a, int32_t* cnt, in
 #pragma unroll
     for (int u = 0; u < SLAB_U; ++u) {
       const int idx = c0 + 64 * u + lane;
-      keep[u] = idx < n_cand;
+      keep[u] = idx < n;
       q[u] = keep[u] ? cand[idx] : q_first;
     }
 #pragma unroll
@@ -431,6 +415,39 @@ __device__ __forceinline__ void slab_candidates(const KArgs& a, int32_t* cnt, in
     push_slab(a, cnt, lane, keep, m, pr);
   }
   __builtin_amdgcn_wave_barrier();
+}
+
+// Gathers the pairs whose bits are set in `hits` (lane's pairs q0 + j) behind
+// the n already in `cand` (SLAB_BLOCK entries); tests and empties the list
+// when it has a round's worth, or no room.  Few pairs of a block lie in one of
+// many slabs: a test per block made as many list appends, all on the objects'
+// few counters, as there are blocks (85 us per slab for 24,000 blocks of a
+// 1080p frame of 1,000 instances; the appends alone set that).
+__device__ __forceinline__ void slab_gather(const KArgs& a, int32_t* cnt, int* cand, int lane, int q0, uint32_t hits,
+                                            int& n) {
+  const int c = __popc(hits);
+  int incl = c;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int y = __shfl_up(incl, off);
+    if (lane >= off) incl += y;
+  }
+  const int more = __shfl(incl, 63);
+  if (more == 0) return;
+  if (n + more > SLAB_BLOCK) {
+    slab_test(a, cnt, cand, lane, n);
+    n = 0;
+  }
+  int k = n + incl - c;
+  while (hits) {
+    cand[k++] = q0 + __ffs(hits) - 1;
+    hits &= hits - 1u;
+  }
+  n += more;
+  if (n >= 64 * SLAB_U) {
+    slab_test(a, cnt, cand, lane, n);
+    n = 0;
+  }
 }
 
 // List S = the pairs of list A in depth slab 0 (objects in mask) whose bound
@@ -457,6 +474,7 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
   const float4* dv = reinterpret_cast<const float4*>(a.pair_dm);
   uint4* sv = reinterpret_cast<uint4*>(a.pair_slab);
   const int wstride = gridDim.x * 4;
+  int n_cand = 0;
   for (int blk = blockIdx.x * 4 + wave; blk < nblk; blk += wstride) {
     const int q0 = blk * SLAB_BLOCK + 16 * lane;
     uint32_t bits = 0, hits = 0;
@@ -497,8 +515,9 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) bits |= __shfl_xor(bits, off);
     if (lane == 0) a.slab_mask[blk] = bits;
-    slab_candidates(a, cnt, s_cand[wave], lane, q0, hits);
+    slab_gather(a, cnt, s_cand[wave], lane, q0, hits, n_cand);
   }
+  if (n_cand > 0) slab_test(a, cnt, s_cand[wave], lane, n_cand);
 }
 
 // List S for slab `slab` >= 1: a wave takes one block of SLAB_BLOCK pairs,
@@ -520,24 +539,32 @@ __global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
   const uint4* sv = reinterpret_cast<const uint4*>(a.pair_slab);
   const uint32_t pat = 0x01010101u * uint32_t(slab);
   const int wstride = gridDim.x * 4;
-  for (int blk = blockIdx.x * 4 + wave; blk < nblk; blk += wstride) {
-    if (!((a.slab_mask[blk] >> slab) & 1u)) continue;
-    const int q0 = blk * SLAB_BLOCK + 16 * lane;
-    uint32_t hits = 0;  // bit j: pair q0 + j is in this slab
-    if (q0 < total) {
-      const uint4 b = sv[q0 / 16];
-      const uint32_t wd[4] = {b.x ^ pat, b.y ^ pat, b.z ^ pat, b.w ^ pat};
+  int n_cand = 0;
+  for (int b0 = blockIdx.x * 4 + wave; b0 < nblk; b0 += 64 * wstride) {
+    // the slab sets of the wave's next 64 blocks at once
+    const int64_t mine = b0 + int64_t(lane) * wstride;
+    uint64_t todo = __ballot(mine < nblk && ((a.slab_mask[mine] >> slab) & 1u));
+    while (todo) {
+      const int blk = b0 + (__ffsll((unsigned long long)todo) - 1) * wstride;
+      todo &= todo - 1;
+      const int q0 = blk * SLAB_BLOCK + 16 * lane;
+      uint32_t hits = 0;  // bit j: pair q0 + j is in this slab
+      if (q0 < total) {
+        const uint4 b = sv[q0 / 16];
+        const uint32_t wd[4] = {b.x ^ pat, b.y ^ pat, b.z ^ pat, b.w ^ pat};
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (((wd[i] >> (8 * j)) & 0xFFu) == 0u) hits |= 1u << (4 * i + j);
-      // bytes past the last pair are ignored
-      const int rem = total - q0;
-      if (rem < 16) hits &= (1u << rem) - 1u;
+          for (int j = 0; j < 4; ++j)
+            if (((wd[i] >> (8 * j)) & 0xFFu) == 0u) hits |= 1u << (4 * i + j);
+        // bytes past the last pair are ignored
+        const int rem = total - q0;
+        if (rem < 16) hits &= (1u << rem) - 1u;
+      }
+      slab_gather(a, cnt, s_cand[wave], lane, q0, hits, n_cand);
     }
-    slab_candidates(a, cnt, s_cand[wave], lane, q0, hits);
   }
+  if (n_cand > 0) slab_test(a, cnt, s_cand[wave], lane, n_cand);
 }
 
 // Depth test of the fallback list (exact): a pair whose ray enters the
