@@ -67,13 +67,15 @@ MAC_CLS = 1008 * 256 + 32 * 256 * 256 + 256 * 193
 # size).  Each record keeps a hash of the kernels' sources; the figure is
 # reported only while they are unchanged.
 NET_SOURCES = ["include/nedf.h"] + ["paper_2308_04669_amd/csrc/" + f for f in (
-    "k_depth.hip", "pipeline.h", "mlp_engine.h", "device_common.h", "launch.h", "runtime.h", "blob_layout.h")]
+    "k_depth.hip", "k_net.hip", "k_march.hip", "k_small.hip", "pipeline.h", "mlp_engine.h", "coop_engine.h",
+    "device_common.h", "launch.h", "runtime.h", "blob_layout.h")]
 TRAFFIC_RECORDS = {
     "infer.nedf/net": os.path.join(ROOT, "profiles", "nedf_net_bf16_batched_1000inst_1920x1080.md"),
     "fallback.mlp": os.path.join(ROOT, "profiles", "fallback_march_bf16_batched_1000inst_1920x1080.md"),
     "train.step": os.path.join(ROOT, "profiles", "train_step_bf16_65536rays.md"),
 }
-TRAIN_SOURCES = ["include/nedf.h"] + ["paper_2308_04669_amd/csrc/" + f for f in ("k_train.hip", "train_layout.h")]
+TRAIN_SOURCES = ["include/nedf.h"] + ["paper_2308_04669_amd/csrc/" + f for f in (
+    "k_train.hip", "k_chain.hip", "train_engine.h", "train_kernels.h", "train_layout.h", "mlp_engine.h")]
 
 
 def sources_hash(files) -> str:
@@ -1124,19 +1126,18 @@ def sphere_labels(o, d, r=0.5):
 
 def train_step_bytes(B, k0=128, width=256, n_hidden=8, n_params=0, splits=16):
     """Algorithmic HBM bytes of one regression-form step as the library runs
-    it: every bfloat16 activation and gradient written once and read by each
-    consumer (next layer, data gradient, weight gradient), ReLU masks as bits,
-    split-K weight-gradient partials written and summed, Adam over float32
-    state (read p, m, v, g; write p, m, v and two bfloat16 copies)."""
+    it: the encoded input and every bfloat16 activation and gradient written
+    once by the forward and backward chain and read once by the weight
+    gradients, ReLU masks as bits, split-K weight-gradient partials written and
+    summed, Adam over float32 state (read p, m, v, g; write p, m, v and two
+    bfloat16 copies)."""
     act, x = B * width * 2, B * k0 * 2
     bits = B * width // 8
-    encode = B * (2 * 12 + 5) + x + B * 8
-    fwd = (x + (n_hidden - 1) * act) + (n_hidden - 1) * (act + bits) + act + B * 8
-    dgrad = (n_hidden - 1) * (act + bits + act)
+    chain = B * (2 * 12 + 5) + x + (n_hidden - 1) * (act + 2 * bits) + n_hidden * act
     wgrad = n_hidden * act + (n_hidden - 1) * act + x
     partials = 2 * splits * width * ((k0 + 1) + (n_hidden - 1) * (width + 1)) * 4
     adam = n_params * (4 * 4 + 3 * 4 + 2 * 2)
-    return encode + fwd + dgrad + wgrad + partials + adam
+    return chain + wgrad + partials + adam
 
 
 def train_bench(args):

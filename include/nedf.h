@@ -486,13 +486,15 @@ int32_t nedf_fp8_calibrate(const nedf_mlp_shape* shape, const float* const* W, c
  * chunk in LDS), the number of 32-row blocks each wave carries through the
  * network (1 or 2; two blocks share every weight read from LDS), the number
  * of persistent workgroups per CU (1 or 2) and the number of 32-row weight
- * chunks streamed into LDS per copy and barrier (1, 2 or 4).  NEDF_TUNE_SLABS is the number of depth slabs in
- * which nedf_infer_depth_id runs the intersection network front to back
- * (1, 2, 4, 8, 16 or 32; an exact pruning: a pair whose smallest possible
- * depth lies beyond the pixel's nearest hit is skipped).  It is kept per
- * kernel and dtype in a process-wide
- * table guarded by a mutex (the library's only global state besides the
- * profiler).
+ * chunks streamed into LDS per copy and barrier (1, 2 or 4).  Short lists take
+ * kernels of their own (with the same results), whatever the value.
+ * NEDF_TUNE_SLABS is the number of depth slabs in which nedf_infer_depth_id
+ * runs the intersection network front to back (1, 2, 4, 8, 16 or 32; an exact
+ * pruning: a pair whose smallest possible depth lies beyond the pixel's
+ * nearest hit is skipped); its initial value, 8, leaves the number to the
+ * library, which chooses by rays x instances of the call.  The values are
+ * kept per kernel and dtype in a process-wide table guarded by a mutex (the
+ * library's only global state besides the profiler).
  *
  * nedf_tune_candidates writes the values instantiated for (kernel, dtype) into
  * out (up to NEDF_TUNE_MAX) and their number into n.  nedf_tune_get/nedf_tune_set read and
