@@ -417,8 +417,8 @@ typedef struct nedf_train_opts {
 
 /* Bytes of the device training state of a network (float32 master weights,
  * Adam moments, last-step gradients, bfloat16 weight copies, step counter),
- * opaque and in the layout of this build of the library; weights move between
- * builds by nedf_train_export and nedf_train_init.
+ * opaque: its layout belongs to the library version that made it, and weights
+ * move between versions by nedf_train_export and nedf_train_init.
  * The network must have width 256 and n_out = 2 (regression form) or be a
  * classifier-form network (NEDF_IN_POINTS16, L10, 1..16 blocks). */
 size_t nedf_train_state_bytes(const nedf_mlp_shape* shape);

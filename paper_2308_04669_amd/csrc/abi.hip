@@ -338,7 +338,7 @@ void run_march(const Prepared& P, int dtype, hipStream_t s) {
 // objects along a ray and more pairs than a few rounds of the chip.  Culling
 // keeps about a tenth of rays x instances, and a round takes 65,536 pairs, so
 // one slab per 4 M rays x instances leaves a slab several rounds: measured
-// on one box, 1 slab against 8: 64 x 64, 8 instances, 0.45 / 0.71 ms; 20,011
+// on one card, 1 slab against 8: 64 x 64, 8 instances, 0.45 / 0.71 ms; 20,011
 // FP32 rays, 24 instances, 2.7 / 4.3 ms; 32 against 8: 1080p, 1,000
 // instances, 25.5 / 32.0 ms; 2 against 8: classifier, 900 x 600, 20
 // instances, 6.0 / 6.5 ms.  A value set in the tuning table is taken as it is.
