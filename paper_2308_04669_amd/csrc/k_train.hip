@@ -247,10 +247,10 @@ __global__ __launch_bounds__(512) void k_gemm(GemmArgs g) {
 // 32 (train_layout.h), which go to LDS as they are, by direct copies of 1 KB
 // (the lanes put the samples in order on the way), 32 samples a stage in a
 // ring of three, and are turned into fragments by transposing reads.  Bound by
-// memory: 538 MB at 65,536 rows and 8 layers.  Turning them in registers
-// (8 x 8 byte permutes between a load and an LDS write) took 32 permutes and a
-// write per 64 values beside the products, and the column sums as many again
-// in half of the waves.
+// memory: 538 MB at 65,536 rows and 8 layers in 132 us (4.1 TB/s; 145 us when
+// they were turned in registers, 32 byte permutes and an LDS write per 64
+// values beside the products, and the column sums as many again in half of
+// the waves), the classifier's 634 MB at 16,384 rows in 176 us (245).
 //
 // Three workgroups share a compute unit (48 KB of LDS each), so that the
 // others' products cover one's waits, and a launch of up to 768 is one round.
