@@ -275,17 +275,36 @@ __device__ __forceinline__ void line_of_local(const float o[3], const float d[3]
   tperp = -(t.hi + t.lo);
 }
 
-// Chord [a, b] of a unit-direction ray inside |x| <= radius, clipped to t >= 0.
-__device__ __forceinline__ bool sphere_chord(const float ol[3], const float dl[3], float radius,
-                                             float& a, float& b) {
-  const float tp = -(ol[0] * dl[0] + ol[1] * dl[1] + ol[2] * dl[2]);
-  const float oo = ol[0] * ol[0] + ol[1] * ol[1] + ol[2] * ol[2];
-  const float h2 = radius * radius - (oo - tp * tp);
+// Sum of squares, written as the fused operations it compiles to: left to the
+// compiler, which products it fuses depends on what else the code around a
+// call computes, and where the sum meets a threshold (a bounding sphere, a
+// field's mask) two kernels that evaluate the same sample would then differ by
+// whole samples.
+__device__ __forceinline__ float sum_sq(float x, float y, float z) { return fmaf(z, z, fmaf(x, x, y * y)); }
+
+// Chord [a, b] of a unit-direction ray inside |x| <= radius, clipped to
+// t >= 0; h2 is the squared half chord.
+__device__ __forceinline__ bool chord_ends(float tp, float h2, float& a, float& b) {
   if (!(h2 > 0.0f)) return false;
   const float h = sqrtf(h2);
   a = fmaxf(tp - h, 0.0f);
   b = tp + h;
   return b > a;
+}
+__device__ __forceinline__ float chord_middle(const float ol[3], const float dl[3]) {
+  return -fmaf(ol[2], dl[2], fmaf(ol[0], dl[0], ol[1] * dl[1]));
+}
+__device__ __forceinline__ bool sphere_chord(const float ol[3], const float dl[3], float radius,
+                                             float& a, float& b) {
+  const float tp = chord_middle(ol, dl);
+  return chord_ends(tp, fmaf(radius, radius, fmaf(tp, tp, -sum_sq(ol[0], ol[1], ol[2]))), a, b);
+}
+// The same from the squared radius, for kernels that have it once per object.
+__device__ __forceinline__ bool sphere_chord_r2(const float ol[3], const float dl[3], float radius2,
+                                                float& a, float& b) {
+#pragma clang fp contract(off)
+  const float tp = chord_middle(ol, dl);
+  return chord_ends(tp, radius2 + fmaf(tp, tp, -sum_sq(ol[0], ol[1], ol[2])), a, b);
 }
 
 // sin(pi y) (h = 0) or cos(pi y) (h = 1) through the hardware sine
@@ -351,11 +370,9 @@ __device__ __forceinline__ uint64_t pack_key(float depth, int id) {
 __device__ __forceinline__ void set_status(int* ws_status, int code) { atomicMax(ws_status, code); }
 
 // Analytic signed distances of the SDF-biased shapes (must match the
-// generator's shape list: sphere, rounded box, torus, ellipsoid).  The sums
-// of squares are written as the fused operations they compile to, in one
-// order: left to the compiler, the order depends on the code around a call,
-// and two kernels of one stage would differ in the last bit.
-__device__ __forceinline__ float norm3(float x, float y, float z) { return sqrtf(fmaf(z, z, fmaf(x, x, y * y))); }
+// generator's shape list: sphere, rounded box, torus, ellipsoid), their sums
+// of squares in one order for every kernel (see sum_sq).
+__device__ __forceinline__ float norm3(float x, float y, float z) { return sqrtf(sum_sq(x, y, z)); }
 __device__ __forceinline__ float sdf_shape(int shape, float x, float y, float z) {
   if (shape == 0) return norm3(x, y, z) - 0.6f;
   if (shape == 1) {

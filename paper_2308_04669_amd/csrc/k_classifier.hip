@@ -100,7 +100,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
       make_ray(a.rays, pr.x, o, d, dlo);
       float tperp;
       local_points_frame(g, o, d, dlo, l, q, dv, tperp, ol);
-      const bool inside = ol[0] * ol[0] + ol[1] * ol[1] + ol[2] * ol[2] < l * l;
+      const bool inside = sum_sq(ol[0], ol[1], ol[2]) < l * l;
       // ray and instance ids (flags in bit 31), t_perp and s, parked in LDS
       // across the network
       eng::lds_write16(stash, eng::u32x4{pr.x | (valid ? 0x80000000u : 0u), pr.y | (inside ? 0x80000000u : 0u),

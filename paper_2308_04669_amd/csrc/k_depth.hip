@@ -578,7 +578,7 @@ __global__ void k_fallback_depth_test(KArgs a, uint2* out) {
   const int lane = threadIdx.x & 63;
   for (int m = 0; m < a.n_obj; ++m) {
     const int cnt = B->cnt[m], off = B->off[m];
-    const float bound = a.obj[m].bound;
+    const float bound2 = a.obj[m].bound * a.obj[m].bound;
     // uniform trip count per wave so that the ballot below sees whole waves
     const int stride = gridDim.x * blockDim.x;
     for (int q0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); q0 < cnt; q0 += stride) {
@@ -591,7 +591,7 @@ __global__ void k_fallback_depth_test(KArgs a, uint2* out) {
         float o[3], d[3], ol[3], dl[3], ta = 0.f, tb = 0.f;
         make_ray(a.rays, pr.x, o, d);
         to_local(g, o, d, ol, dl);
-        const bool seg = a.clip ? sphere_chord(ol, dl, bound, ta, tb) : true;
+        const bool seg = a.clip ? sphere_chord_r2(ol, dl, bound2, ta, tb) : true;
         const float t_in = a.clip ? g.s * ta : a.t_near;
         keep = seg && !(depth_limit(a, pr.x) < t_in);
       }
@@ -614,6 +614,7 @@ __global__ void k_march_analytic(KArgs a, uint32_t mask) {
     const ObjDesc od = a.obj[m];
     if (od.field == NEDF_FIELD_MLP || !((mask >> m) & 1u)) continue;
     const int cnt = a.lcnt[m], off = a.loff[m];
+    const float bound2 = od.bound * od.bound;
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < cnt; q += gridDim.x * blockDim.x) {
       const uint2 pr = a.pairs[off + q];
       const W2L g = load_w2l(a.w2l, int(pr.y));
@@ -622,7 +623,7 @@ __global__ void k_march_analytic(KArgs a, uint32_t mask) {
       to_local(g, o, d, ol, dl);
       float ta, tb;
       if (a.clip) {
-        if (!sphere_chord(ol, dl, od.bound, ta, tb)) continue;
+        if (!sphere_chord_r2(ol, dl, bound2, ta, tb)) continue;
       } else {
         ta = a.t_near * g.inv_s;
         tb = a.t_far * g.inv_s;

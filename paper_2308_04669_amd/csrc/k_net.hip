@@ -67,7 +67,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_nedf(KArgs a) {
       float o[3], d[3], dlo[3], ol[3], pl[6], pllo[6], tperp;
       make_ray(a.rays, pr.x, o, d, dlo);
       local_line(g, o, d, dlo, pl, pllo, tperp, ol);
-      const bool inside = ol[0] * ol[0] + ol[1] * ol[1] + ol[2] * ol[2] < l * l;
+      const bool inside = sum_sq(ol[0], ol[1], ol[2]) < l * l;
       eng::encode_input<DT, 6, L, KS0>(pl, pllo, half_v, Benc[nb], in_scale);
       // ray and instance ids (< 2^31, flags in bit 31), t_perp and s
       eng::lds_write16(stash + uint32_t(nb) * (16u * NT),

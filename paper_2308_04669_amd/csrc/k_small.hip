@@ -45,7 +45,7 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_nedf_small(KArgs a) {
     float o[3], d[3], dlo[3], ol[3], pl[6], pllo[6], tperp;
     make_ray(a.rays, pr.x, o, d, dlo);
     local_line(g, o, d, dlo, pl, pllo, tperp, ol);
-    const bool inside = ol[0] * ol[0] + ol[1] * ol[1] + ol[2] * ol[2] < l * l;
+    const bool inside = sum_sq(ol[0], ol[1], ol[2]) < l * l;
     float y[1][2];
     coop::network<DT, KS0, 8, 2, 1>(
         hb, blob, lds, [&](int, auto rc) { return coop::encode_read<DT, 6, L>(pl, pllo, half, rc); }, y);

@@ -92,7 +92,7 @@ __device__ __forceinline__ float mlp_sigma(const ObjDesc& od, float u, float x, 
     return od.param[0] * sigmoidf_(u - sdf_shape(int(od.param[2]), x, y, z) / od.param[1]);
   const float s = softplusf_(u);
   if (od.sigma_mode == NEDF_SIGMA_SOFTPLUS_MASKED)
-    return (x * x + y * y + z * z <= od.bound * od.bound) ? s : 0.0f;
+    return sum_sq(x, y, z) <= od.bound * od.bound ? s : 0.0f;
   return s;
 }
 
