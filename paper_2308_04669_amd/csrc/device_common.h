@@ -371,8 +371,23 @@ __device__ __forceinline__ void set_status(int* ws_status, int code) { atomicMax
 
 // Analytic signed distances of the SDF-biased shapes (must match the
 // generator's shape list: sphere, rounded box, torus, ellipsoid), their sums
-// of squares in one order for every kernel (see sum_sq).
+// of squares in one order for every kernel (see sum_sq).  The torus has two
+// roundings, apart by units in the last place: that of the marched density
+// (MARCH; plain products under the inner root) and that of the surface
+// function and the shaded density.  Each is kept, so that depth, refined depth
+// and colour stay what they were.
 __device__ __forceinline__ float norm3(float x, float y, float z) { return sqrtf(sum_sq(x, y, z)); }
+template <bool MARCH>
+__device__ __forceinline__ float sdf_torus(float x, float y, float z) {
+  if constexpr (MARCH) {
+#pragma clang fp contract(off)
+    const float qx = sqrtf(x * x + z * z) - 0.5f;
+    return sqrtf(fmaf(qx, qx, y * y)) - 0.2f;
+  }
+  const float qx = sqrtf(fmaf(x, x, z * z)) - 0.5f;
+  return sqrtf(fmaf(y, y, qx * qx)) - 0.2f;
+}
+template <bool MARCH = false>
 __device__ __forceinline__ float sdf_shape(int shape, float x, float y, float z) {
   if (shape == 0) return norm3(x, y, z) - 0.6f;
   if (shape == 1) {
@@ -380,10 +395,7 @@ __device__ __forceinline__ float sdf_shape(int shape, float x, float y, float z)
     const float mx = fmaxf(qx, 0.f), my = fmaxf(qy, 0.f), mz = fmaxf(qz, 0.f);
     return norm3(mx, my, mz) + fminf(fmaxf(qx, fmaxf(qy, qz)), 0.f) - 0.05f;
   }
-  if (shape == 2) {
-    const float qx = sqrtf(fmaf(x, x, z * z)) - 0.5f;
-    return sqrtf(fmaf(y, y, qx * qx)) - 0.2f;
-  }
+  if (shape == 2) return sdf_torus<MARCH>(x, y, z);
   const float ax = x / 0.7f, ay = y / 0.45f, az = z / 0.35f;
   const float bx = x / 0.49f, by = y / 0.2025f, bz = z / 0.1225f;
   const float k0 = norm3(ax, ay, az), k1 = norm3(bx, by, bz);

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_march_mlp(KArgs a) {
         const float tr = (float(si) + 0.5f) * delta;
         const float p[3] = {fmaf(tr, dl[0], pa[0]), fmaf(tr, dl[1], pa[1]), fmaf(tr, dl[2], pa[2])};
         const float u = partial[nb][0] + __shfl_xor(partial[nb][0], 32) + head_b;
-        float v = mlp_sigma(od, u, p[0], p[1], p[2]) * delta;
+        float v = mlp_sigma<true>(od, u, p[0], p[1], p[2]) * delta;
         if (lane >= 32 || si >= N || !seg) v = 0.f;
         sum.add(v, ta + tr, lane);
       }

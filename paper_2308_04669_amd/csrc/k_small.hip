@@ -105,7 +105,7 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
       if (threadIdx.x < 64) {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          float v = mlp_sigma(od, y[nb][0] + head_b, p[nb][0], p[nb][1], p[nb][2]) * delta;
+          float v = mlp_sigma<true>(od, y[nb][0] + head_b, p[nb][0], p[nb][1], p[nb][2]) * delta;
           if (lane >= 32 || s0 + 32 * nb + (lane & 31) >= N) v = 0.f;
           sum.add(v, ta + tr[nb], lane);
         }

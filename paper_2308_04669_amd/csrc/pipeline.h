@@ -86,10 +86,12 @@ __device__ __forceinline__ float analytic_sigma(const ObjDesc& od, float x, floa
   return (z >= od.param[1] && z <= od.param[2]) ? od.param[0] : 0.0f;
 }
 
-// Density of an MLP field from the raw head output u at local point x.
+// Density of an MLP field from the raw head output u at local point x (MARCH:
+// as a marcher's sample, see sdf_shape).
+template <bool MARCH = false>
 __device__ __forceinline__ float mlp_sigma(const ObjDesc& od, float u, float x, float y, float z) {
   if (od.sigma_mode == NEDF_SIGMA_SDF)
-    return od.param[0] * sigmoidf_(u - sdf_shape(int(od.param[2]), x, y, z) / od.param[1]);
+    return od.param[0] * sigmoidf_(u - sdf_shape<MARCH>(int(od.param[2]), x, y, z) / od.param[1]);
   const float s = softplusf_(u);
   if (od.sigma_mode == NEDF_SIGMA_SOFTPLUS_MASKED)
     return sum_sq(x, y, z) <= od.bound * od.bound ? s : 0.0f;
