@@ -460,7 +460,9 @@ extern "C" int32_t nedf_ws_counters(const void* ws, nedf_stream_t stream, int64_
   out7[2] = c.stats[0];
   out7[3] = c.stats[1];
   out7[4] = c.stats[2];
-  out7[5] = c.stats[3];
+  // totalled here: a call that makes keys alone runs no kernel after the marcher
+  out7[5] = 0;
+  for (int m = 0; m < NEDF_MAX_OBJECTS; ++m) out7[5] += c.B.fill[m];
   out7[6] = c.stats[4];
   return NEDF_OK;
 }

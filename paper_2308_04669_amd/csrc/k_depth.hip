@@ -650,19 +650,13 @@ __global__ void k_march_analytic(KArgs a, uint32_t mask) {
 
 // Keys -> depth, id and opacity.  A workgroup takes a contiguous range of
 // rays; with BIN it also counts its hit pixels per object of `mask` for the
-// binning that follows (one global atomic per workgroup and object).  The
-// first workgroup totals the marched fallback pairs.
+// binning that follows (one global atomic per workgroup and object).
 template <bool BIN>
 __global__ __launch_bounds__(256) void k_finalize(KArgs a, uint32_t mask) {
   __shared__ int s_cnt[NEDF_MAX_OBJECTS];
   const int t = threadIdx.x, lane = t & 63;
   if (BIN && t < NEDF_MAX_OBJECTS) s_cnt[t] = 0;
   if (BIN) __syncthreads();
-  if (blockIdx.x == 0 && t < 64) {
-    int kept;
-    wave_prefix(t < a.n_obj ? a.C->B.fill[t] : 0, t, kept);
-    if (t == 0) a.C->stats[3] = kept;
-  }
   const int64_t per = bin_span(a.n_rays, gridDim.x);
   const int64_t p0 = int64_t(blockIdx.x) * per;
   const int64_t p1 = min(p0 + per, a.n_rays);

@@ -11,16 +11,14 @@ namespace nedf {
 namespace {
 
 // Start of the shading call: the status word, list R and (for the outliers)
-// list B.
+// the counts of list B (its fill counters are the depth call's).
 __global__ void k_begin_pixels(KArgs a, int resample) {
   const int t = threadIdx.x;
   constexpr int words = int(sizeof(PairList) / 4);
   if (t == 0) *a.status = 0;
-  for (int i = t; i < words; i += blockDim.x) {
-    reinterpret_cast<int32_t*>(&a.C->R)[i] = 0;
-    if (resample) reinterpret_cast<int32_t*>(&a.C->B)[i] = 0;
-  }
-  if (t == 0 && resample) a.C->stats[1] = 0;
+  for (int i = t; i < words; i += blockDim.x) reinterpret_cast<int32_t*>(&a.C->R)[i] = 0;
+  if (resample && t < NEDF_MAX_OBJECTS) a.C->B.cnt[t] = 0;
+  if (t == 0 && resample) a.C->B.work_counter = a.C->stats[1] = 0;
 }
 
 // Pairs of list R: pixels with a valid ID whose object is in `mask`, as

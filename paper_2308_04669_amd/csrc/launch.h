@@ -36,7 +36,7 @@ struct PairList {
 // Device counters in the workspace (after the 256-byte status block).
 struct WsCounters {
   PairList A;       // primary pairs (culling result)
-  PairList B;       // fallback pairs (NeDF uncertain rays); fill: those left after the depth test
+  PairList B;       // fallback pairs (NeDF uncertain rays); fill: those left after the depth test (marched)
   PairList R;       // pixels binned by object (refinement, shading)
   // pairs of the current depth slab of the network stage, in the segments of
   // list A: slab k counts in set k % 2 while its filter clears the other set
@@ -44,7 +44,7 @@ struct WsCounters {
   int32_t slab_work[2];
   int32_t last_pairs, last_items;  // of the list binned last
   int32_t stats[8]; // [0] pairs decided by the network, [1] sent to the marcher, [2] network misses,
-                    // [3] marcher pairs left after the depth test, [4] pairs after culling
+                    // [4] pairs after culling
   uint32_t dmin_bits, dmax_bits;  // range of the pairs' lowest possible depths (float bits, >= 0)
 };
 
