@@ -345,7 +345,7 @@ void run_march(const Prepared& P, int dtype, hipStream_t s) {
 int depth_slabs(const KArgs& k, int dtype) {
   const int dt = dtype == NEDF_FP8_MX ? NEDF_FP8 : dtype;  // MX networks take the FP8 entry
   const int v = tune_value(NEDF_TUNE_SLABS, dt);
-  if (v != NEDF_SLABS_DEFAULT) return v;
+  if (v != NEDF_SLABS_AUTO) return v;
   const int64_t most = std::min<int64_t>(k.capacity, k.n_rays * k.n_inst);
   int s = 1;
   while (s < 32 && 2 * s <= k.n_inst && most >= int64_t(2 * s) << 22) s *= 2;
@@ -941,8 +941,8 @@ namespace {
 std::mutex g_tune_mu;
 // [kernel][dtype]: 10 * workgroups per CU + chunks per superchunk; for
 // NEDF_TUNE_SLABS the number of depth slabs of the network stage
-// (NEDF_SLABS_DEFAULT: chosen by the size of the call)
-int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 1014}, {NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT, NEDF_SLABS_DEFAULT}};
+// (NEDF_SLABS_AUTO: chosen by the size of the call)
+int g_tune[3][3] = {{11, 1012, 14}, {11, 1012, 1014}, {NEDF_SLABS_AUTO, NEDF_SLABS_AUTO, NEDF_SLABS_AUTO}};
 
 int tune_candidates(int kernel, int dtype, int32_t* out) {
   if (kernel < 0 || kernel > 2 || dtype < 0 || dtype > 2) return 0;
@@ -990,7 +990,7 @@ extern "C" int32_t nedf_tune_set(int32_t kernel, int32_t dtype, int32_t value) {
   int32_t c[NEDF_TUNE_MAX];
   const int n = tune_candidates(kernel, dtype, c);
   if (n == 0) return fail(NEDF_ERR_UNSUPPORTED, "no tunable kernel for this (kernel, dtype)");
-  bool ok = false;
+  bool ok = kernel == NEDF_TUNE_SLABS && value == NEDF_SLABS_AUTO;
   for (int i = 0; i < n; ++i) ok |= c[i] == value;
   if (!ok) return fail(NEDF_ERR_UNSUPPORTED, "value is not an instantiated candidate");
   std::lock_guard<std::mutex> lk(g_tune_mu);

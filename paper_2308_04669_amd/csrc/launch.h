@@ -74,9 +74,9 @@ bool refine_supported(int dtype, const nedf_mlp_shape& s);
 
 struct KArgs;
 
-// Initial value of NEDF_TUNE_SLABS: the number of depth slabs is chosen by
+// Initial value of NEDF_TUNE_SLABS (not a number of slabs): it is chosen by
 // the size of the call.
-constexpr int NEDF_SLABS_DEFAULT = 8;
+constexpr int NEDF_SLABS_AUTO = 0;
 
 int cu_count();
 
