@@ -153,7 +153,7 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_refine_small(KArgs a) {
       for (int nb = 0; nb < NB; ++nb) f[nb] = mlp_surface(od, y[nb][0] + head_b, p[nb][0], p[nb][1], p[nb][2]);
     };
     Secant s;
-    s.start(a.depth[pr.x], a.refine_h * g.s);
+    s.start<DT == 1>(a.depth[pr.x], a.refine_h, g.s);
     {
       const float t[2] = {s.t0, s.t1};
       float f[2];

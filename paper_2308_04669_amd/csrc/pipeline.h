@@ -240,8 +240,20 @@ __device__ __forceinline__ void flush_routing(const KArgs& a, int lane, const in
 struct Secant {
   float t0, t1, f0, f1, out, lo, hi;
   bool active;
-  __device__ void start(float D, float h) {
-    t0 = D - h; t1 = D + h; out = D; lo = D - 2.f * h; hi = D + 2.f * h;
+  // Seeds around D at h = rh * s.  Left to the compiler, whether a seed's
+  // product is rounded before the sum depends on where in the kernel the seed
+  // is used, and two kernels would start from neighbouring values.  The upper
+  // seed has two roundings (ROUNDED: that of the BF16 networks), each kept so
+  // that refined depths stay what they were.
+  template <bool ROUNDED = false>
+  __device__ void start(float D, float rh, float s) {
+#pragma clang fp contract(off)
+    const float h = rh * s;
+    t0 = fmaf(-rh, s, D);
+    t1 = ROUNDED ? D + h : fmaf(rh, s, D);
+    out = D;
+    lo = fmaf(-2.f, h, D);
+    hi = fmaf(2.f, h, D);
   }
   __device__ float update() {  // returns the new iterate (evaluation point)
     const float den = f1 - f0;
