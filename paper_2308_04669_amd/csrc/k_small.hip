@@ -60,11 +60,13 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_nedf_small(KArgs a) {
   if (threadIdx.x < 64) flush_routing(a, lane, n_route);
 }
 
-// Marcher: a workgroup takes one pair at a time, 32 NB samples per pass.
-template <int DT, int NB>
+// Marcher: a workgroup takes one pair at a time, 64 samples per pass and the
+// last 32 or fewer in a pass of their own (FP32, 160 x 160 rays, 16 objects, 32
+// samples: 6.3 ms with half of every pass empty, 3.6 without).
+template <int DT>
 __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
   constexpr int L = 10, KS0 = eng::ks_for_slots<DT>(3 * L + 2);
-  __shared__ __attribute__((aligned(16))) uint8_t lds[coop::Lds<DT, NB, 1>::BYTES];
+  __shared__ __attribute__((aligned(16))) uint8_t lds[coop::Lds<DT, 2, 1>::BYTES];
   __shared__ ItemTable s_tab;
   if (!build_items<ROUTE_SMALL>(a, s_tab, 1)) return;
   const int lane = threadIdx.x & 63, half = lane >> 5;
@@ -90,7 +92,8 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
     const float delta = (tb - ta) / float(N);
     const float pa[3] = {fmaf(ta, dl[0], ol[0]), fmaf(ta, dl[1], ol[1]), fmaf(ta, dl[2], ol[2])};
     MarchSum sum;
-    for (int s0 = 0; s0 < N; s0 += 32 * NB) {
+    auto pass = [&](auto nbc, int s0) __attribute__((always_inline)) {
+      constexpr int NB = decltype(nbc)::value;
       float tr[NB], p[NB][3];
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
@@ -110,7 +113,10 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
           sum.add(v, ta + tr[nb], lane);
         }
       }
-    }
+    };
+    int s0 = 0;
+    for (; N - s0 > 32; s0 += 64) pass(std::integral_constant<int, 2>{}, s0);
+    if (s0 < N) pass(std::integral_constant<int, 1>{}, s0);
     if (threadIdx.x == 0) sum.emit(a, pr, g.s);
   }
 }
@@ -182,8 +188,8 @@ void launch_nedf_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) 
 }
 
 void launch_march_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) {
-  if (dtype == NEDF_BF16) hipLaunchKernelGGL((k_march_small<1, 2>), dim3(grid), dim3(coop::THREADS), 0, s, k);
-  else hipLaunchKernelGGL((k_march_small<0, 2>), dim3(grid), dim3(coop::THREADS), 0, s, k);
+  if (dtype == NEDF_BF16) hipLaunchKernelGGL(k_march_small<1>, dim3(grid), dim3(coop::THREADS), 0, s, k);
+  else hipLaunchKernelGGL(k_march_small<0>, dim3(grid), dim3(coop::THREADS), 0, s, k);
 }
 
 void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) {
