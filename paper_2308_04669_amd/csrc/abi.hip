@@ -341,12 +341,14 @@ void run_march(const Prepared& P, int dtype, hipStream_t s) {
 // on one card, 1 slab against 8: 64 x 64, 8 instances, 0.45 / 0.71 ms; 20,011
 // FP32 rays, 24 instances, 2.7 / 4.3 ms; 32 against 8: 1080p, 1,000
 // instances, 25.5 / 32.0 ms; 2 against 8: classifier, 900 x 600, 20
-// instances, 6.0 / 6.5 ms.  A value set in the tuning table is taken as it is.
+// instances, 6.0 / 6.5 ms.  (Not by the workspace's capacity: that is sized by
+// anything between rays x instances and the culled pairs, and a tight one would
+// be given fewer slabs.)  A value set in the tuning table is taken as it is.
 int depth_slabs(const KArgs& k, int dtype) {
   const int dt = dtype == NEDF_FP8_MX ? NEDF_FP8 : dtype;  // MX networks take the FP8 entry
   const int v = tune_value(NEDF_TUNE_SLABS, dt);
   if (v != NEDF_SLABS_AUTO) return v;
-  const int64_t most = std::min<int64_t>(k.capacity, k.n_rays * k.n_inst);
+  const int64_t most = k.n_rays * k.n_inst;
   int s = 1;
   while (s < 32 && 2 * s <= k.n_inst && most >= int64_t(2 * s) << 22) s *= 2;
   return s;
