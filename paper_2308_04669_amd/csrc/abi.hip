@@ -333,25 +333,38 @@ void run_march(const Prepared& P, int dtype, hipStream_t s) {
 }
 
 // Depth slabs of the network stage.  Each slab beyond the first costs a filter
-// and a launch (about 10 us, and the chip empties at the end of each) and
-// saves the pairs hidden behind the slabs before it, which takes several
-// objects along a ray and more pairs than a few rounds of the chip.  Culling
-// keeps about a tenth of rays x instances, and a round takes 65,536 pairs, so
-// one slab per 4 M rays x instances leaves a slab several rounds: measured
-// on one card, 1 slab against 8: 64 x 64, 8 instances, 0.45 / 0.71 ms; 20,011
-// FP32 rays, 24 instances, 2.7 / 4.3 ms; 32 against 8: 1080p, 1,000
-// instances, 25.5 / 32.0 ms; 2 against 8: classifier, 900 x 600, 20
-// instances, 6.0 / 6.5 ms.  (Not by the workspace's capacity: that is sized by
-// anything between rays x instances and the culled pairs, and a tight one would
-// be given fewer slabs.)  A value set in the tuning table is taken as it is.
-int depth_slabs(const KArgs& k, int dtype) {
+// and a network launch (about 10 us when the slab is empty; the chip empties at
+// the end of a full one) and saves the pairs hidden behind the slabs before it.
+// How many are hidden depends on the pairs that culling keeps, a twentieth to
+// two thirds of rays x instances, and these are known on the device only.  So
+// the host launches the slabs that the densest scene of this size pays for, and
+// the first filter uses as many of them as leave each `per_slab` pairs (the
+// others end at once).  per_slab is 6 rounds of the networks on the chip, 5
+// rounds in FP32, whose pairs take 17 times as long.  Measured on one card,
+// milliseconds for 1 / 2 / 4 / 8 slabs; BF16: 320 x 180, 60 instances, 267 K
+// pairs 0.67 / 0.68 / 0.78 / 1.0 (0.70 with the second slab launched and not
+// used), 1,978 K pairs 2.2 / 1.8 / 1.6 / 1.8; 900 x 600, 14 instances, 639 K
+// 1.6 / 1.7 / 1.9 / 2.1, 4,476 K 5.0 / 4.1 / 3.8 / 4.1; FP32: 320 x 180, 60
+// instances, 267 K 4.5 / 4.0 / 3.9 / 4.0, 1,978 K 19.8 / 15.3 / 11.5 / 10.7;
+// classifier: 900 x 600, 14 instances, 585 K 2.8 / 2.8 / 3.1 / 3.6, 4,221 K
+// 15.8 / 11.5 / 10.4 / 9.6; 32 against 8 slabs at 1080p, 1,000 instances: 25.5
+// / 32.0.  (Rays x instances, not the workspace's
+// capacity: that is sized by anything from the culled pairs up, and a tight one
+// would be given fewer slabs.)  A value set in the tuning table is taken as it is.
+SlabPlan depth_slabs(const KArgs& k, int dtype, bool classifier) {
   const int dt = dtype == NEDF_FP8_MX ? NEDF_FP8 : dtype;  // MX networks take the FP8 entry
   const int v = tune_value(NEDF_TUNE_SLABS, dt);
-  if (v != NEDF_SLABS_AUTO) return v;
+  if (v != NEDF_SLABS_AUTO) return {v, 0};
   const int64_t most = k.n_rays * k.n_inst;
-  int s = 1;
-  while (s < 32 && 2 * s <= k.n_inst && most >= int64_t(2 * s) << 22) s *= 2;
-  return s;
+  // rays x instances from which n slabs are launched: the first few by the cost
+  // of a pair against that of a launch (two per slab of the classifier's), more
+  // where even a sparse scene fills them
+  const auto need = [&](int64_t n) {
+    return n > (classifier ? 4 : 8) ? n << 22 : dtype == NEDF_F32 ? n << 18 : classifier ? n << 19 : n * n << 19;
+  };
+  SlabPlan p{1, dtype == NEDF_F32 ? 5 * 8192 : 6 * 65536};
+  while (p.n < 32 && 2 * p.n <= k.n_inst && most >= need(2 * p.n)) p.n *= 2;
+  return p;
 }
 
 // NeDF depth keys (+ fallback) of every pair into k.keys.
@@ -364,7 +377,7 @@ void run_infer_keys(const Prepared& P, int dtype, const nedf_infer_opts& o, hipS
   const uint32_t direct = P.analytic & ~P.nedf;
   if (direct) stage_march(k, s, false, direct, dtype, 0, 0, 0);
   if (!P.nedf) return;
-  stage_nedf(k, s, P.nedf_dtype, P.nedf, depth_slabs(k, P.nedf_dtype), P.nedf_cls);
+  stage_nedf(k, s, P.nedf_dtype, P.nedf, depth_slabs(k, P.nedf_dtype, P.nedf_cls), P.nedf_cls);
   // uncertain pairs: marcher on list B
   stage_march(k, s, true, P.analytic, dtype, (P.mlp & P.nedf) ? P.W : 0, P.H, P.L);
 }

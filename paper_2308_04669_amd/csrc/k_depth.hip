@@ -450,13 +450,22 @@ __device__ __forceinline__ void slab_gather(const KArgs& a, int32_t* cnt, int* c
   }
 }
 
+// Slabs in use of those launched: the most that leave each plan.per_slab of
+// the culled pairs on average (SlabPlan; uniform over the grid).
+__device__ __forceinline__ int slabs_used(const SlabPlan& plan, int total) {
+  if (plan.per_slab == 0) return plan.n;
+  int n = 1;
+  while (2 * n <= plan.n && int64_t(2 * n) * plan.per_slab <= total) n *= 2;
+  return n;
+}
+
 // List S = the pairs of list A in depth slab 0 (objects in mask) whose bound
 // does not lie beyond the pixel's current nearest hit.  Also records every
 // pair's slab in one byte (0xFF for objects outside the mask) and, per block
 // of SLAB_BLOCK pairs, the set of slabs present, so that the later slabs skip
 // blocks without their pairs and read one byte per pair in the others.  A
 // wave takes one block: sixteen consecutive pairs per lane.
-__global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int n_slabs) {
+__global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, SlabPlan plan) {
   __shared__ int s_cand[4][SLAB_BLOCK];
   __shared__ int s_off[NEDF_MAX_OBJECTS + 1];
   const PairList* A = &a.C->A;
@@ -466,10 +475,11 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
   // global memory, so the compiler could not keep them in registers)
   if (threadIdx.x <= a.n_obj) s_off[threadIdx.x] = A->off[threadIdx.x];
   const float lo = __uint_as_float(a.C->dmin_bits), hi = __uint_as_float(a.C->dmax_bits);
-  const bool single = n_slabs <= 1 || !(hi > lo);
-  const float inv_w = single ? 0.0f : float(n_slabs) / (hi - lo);
   __syncthreads();
   const int total = s_off[a.n_obj];
+  const int n_slabs = slabs_used(plan, total);
+  const bool single = n_slabs <= 1 || !(hi > lo);
+  const float inv_w = single ? 0.0f : float(n_slabs) / (hi - lo);
   const int nblk = (total + SLAB_BLOCK - 1) / SLAB_BLOCK;
   const float4* dv = reinterpret_cast<const float4*>(a.pair_dm);
   uint4* sv = reinterpret_cast<uint4*>(a.pair_slab);
@@ -520,10 +530,10 @@ __global__ __launch_bounds__(256) void k_slab_first(KArgs a, uint32_t mask, int 
   if (n_cand > 0) slab_test(a, cnt, s_cand[wave], lane, n_cand);
 }
 
-// List S for slab `slab` >= 1: a wave takes one block of SLAB_BLOCK pairs,
+// List S for slab `slab` >= 1 (of those in use): a wave takes one block of SLAB_BLOCK pairs,
 // skips it unless its slab set holds `slab`, else scans the slab bytes
 // (sixteen per lane, one 16-byte load) and tests the matching pairs.
-__global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
+__global__ __launch_bounds__(256) void k_slab_next(KArgs a, SlabPlan plan, int slab) {
   __shared__ int s_cand[4][SLAB_BLOCK];
   const PairList* A = &a.C->A;
   int32_t* cnt = a.C->slab_cnt[slab & 1];
@@ -535,6 +545,7 @@ __global__ __launch_bounds__(256) void k_slab_next(KArgs a, int slab) {
     if (threadIdx.x == 0) a.C->slab_work[(slab + 1) & 1] = 0;
   }
   const int total = A->off[a.n_obj];
+  if (slab >= slabs_used(plan, total)) return;  // its list stays empty
   const int nblk = (total + SLAB_BLOCK - 1) / SLAB_BLOCK;
   const uint4* sv = reinterpret_cast<const uint4*>(a.pair_slab);
   const uint32_t pat = 0x01010101u * uint32_t(slab);
@@ -830,7 +841,7 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   }
 }
 
-void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, int n_slabs, bool classifier) {
+void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, SlabPlan slabs, bool classifier) {
   KArgs k = k0;
   prof_mark("infer.nedf", s, true);
   k.item_mask = nedf_mask;
@@ -848,8 +859,8 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, i
   // large calls), so it takes list A as it is
   bool others = k.ray_tmax != nullptr;
   for (int m = 0; m < k.n_obj; ++m) others |= !((nedf_mask >> m) & 1u);
-  const bool direct = n_slabs == 1 && !(others && pair_bound(k) > (1 << 20));
-  for (int slab = 0; slab < n_slabs; ++slab) {
+  const bool direct = slabs.n == 1 && !(others && pair_bound(k) > (1 << 20));
+  for (int slab = 0; slab < slabs.n; ++slab) {
     if (direct) {
       k.lcnt = k.C->A.cnt;
       k.lwork = &k.C->slab_work[0];
@@ -857,14 +868,14 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, i
       k.pairs = k.pairsS;
       k.lcnt = k.C->slab_cnt[slab & 1];
       k.lwork = &k.C->slab_work[slab & 1];
-      if (slab == 0) hipLaunchKernelGGL(k_slab_first, fg, dim3(256), 0, s, k0, nedf_mask, n_slabs);
-      else hipLaunchKernelGGL(k_slab_next, fg, dim3(256), 0, s, k0, slab);
+      if (slab == 0) hipLaunchKernelGGL(k_slab_first, fg, dim3(256), 0, s, k0, nedf_mask, slabs);
+      else hipLaunchKernelGGL(k_slab_next, fg, dim3(256), 0, s, k0, slabs, slab);
     }
     prof_mark("net", s, true);
     if (classifier) launch_nedf_cls(k, s, dtype, pair_bound(k));
     else {
       Kernels kn{false, true};
-      if (dtype == NEDF_F32 || (dtype == NEDF_BF16 && n_slabs == 1))
+      if (dtype == NEDF_F32 || (dtype == NEDF_BF16 && slabs.n == 1))
         kn = choose_kernels(k, dtype, 32, 3 * cu_count(), pair_bound(k));
       if (kn.small) launch_nedf_small(k, s, dtype, cu_count());
       if (kn.large) launch_nedf(k, s, dtype, v);

@@ -121,9 +121,13 @@ void launch_nedf(const KArgs& k, hipStream_t s, int dtype, int v);
 void stage_init_cull(const KArgs& k, hipStream_t s, uint32_t item_mask, int item_pairs);
 void stage_march(const KArgs& k, hipStream_t s, bool list_b, uint32_t analytic_mask, int dtype, int W, int H,
                  int L);
-// Intersection-network stage over list A, front to back in n_slabs depth
+// Intersection-network stage over list A, front to back in up to slabs.n depth
 // slabs (objects in nedf_mask).
-void stage_nedf(const KArgs& k, hipStream_t s, int dtype, uint32_t nedf_mask, int n_slabs,
+struct SlabPlan {
+  int n;         // slabs launched
+  int per_slab;  // culled pairs that make a slab worth using (0: all n are used)
+};
+void stage_nedf(const KArgs& k, hipStream_t s, int dtype, uint32_t nedf_mask, SlabPlan slabs,
                 bool classifier = false);
 // Classifier-form networks (NEDF_IN_POINTS16) over the current slab list; the
 // BF16 lists of one round of four-wave items go to that kernel, longer ones to
