@@ -738,7 +738,6 @@ Kernels choose_kernels(KArgs& k, int dtype, int per, int most, int64_t bound) {
   k.split_per = 0;
   if (dtype == NEDF_F32) return {true, false};
   if ((bound + per - 1) / per + k.n_obj <= most) return {true, false};
-  if (k.n_rays > (int64_t(1) << 20)) return {false, true};
   k.split_per = per;
   k.split_max = most;
   return {true, true};

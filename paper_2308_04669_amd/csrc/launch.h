@@ -105,8 +105,9 @@ void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid
 // its 4 serial passes of 38 us).
 // `bound` is the host's bound on the pairs; if it does not decide, both are
 // launched and the device's counts decide (the other ends at once, about
-// 4 us), except in calls of more than 2^20 rays, where such a list would save
-// less than that launch costs every other call.
+// 4 us).  That holds for large calls too: a small object in a frame of 1.1 M
+// rays leaves 756 marched pairs and 300 refined pixels, 174 and 149 us on the
+// large kernels and 130 and 55 us on these.
 struct Kernels {
   bool small, large;
 };
