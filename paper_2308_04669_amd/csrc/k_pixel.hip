@@ -25,7 +25,8 @@ __global__ void k_begin_pixels(KArgs a, int resample) {
 // (pixel, instance), after their counts per object (k_finalize or
 // k_clear_rgb): the workgroup counts its own pixels, reserves one range per
 // object and writes.  The first workgroup records the segments and the work
-// items over item_mask.
+// items over item_mask.  Objects outside `mask` keep their counts and get no
+// segment.
 __global__ __launch_bounds__(256) void k_bin_write(KArgs a, const int32_t* ids, uint32_t mask) {
   __shared__ int s_cnt[NEDF_MAX_OBJECTS], s_base[NEDF_MAX_OBJECTS], s_seg[NEDF_MAX_OBJECTS], s_lim[NEDF_MAX_OBJECTS];
   const int t = threadIdx.x, lane = t & 63;
@@ -34,7 +35,8 @@ __global__ __launch_bounds__(256) void k_bin_write(KArgs a, const int32_t* ids, 
   const int64_t p1 = p0 + per < a.n_rays ? p0 + per : a.n_rays;
   PairList* L = &a.C->R;
   if (t < 64) {
-    const int64_t c = t < a.n_obj ? L->cnt[t] : 0;
+    const bool listed = t < a.n_obj && ((mask >> t) & 1u);
+    const int64_t c = listed ? L->cnt[t] : 0;
     int64_t total;
     const int64_t off = wave_prefix(c, t, total);
     const int64_t o0 = min(off, a.capacity), lim = min(off + c, a.capacity) - o0;
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(256) void k_bin_write(KArgs a, const int32_t* ids, 
       wave_prefix(counted ? int((lim + a.item_pairs - 1) / a.item_pairs) : 0, t, items);
       wave_prefix(counted ? int(lim) : 0, t, pairs);
       if (t <= a.n_obj) L->off[t] = int(o0);
-      if (t < a.n_obj) L->cnt[t] = int(lim);
+      if (listed) L->cnt[t] = int(lim);
       if (t == 0) {
         a.C->last_pairs = pairs;
         a.C->last_items = items;
@@ -436,9 +438,18 @@ void stage_refine(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t m
   // stream it twice; the refinement is bound by that L2 -> LDS stream, and the
   // 8-wave form measured 8 % faster on the 1080p frame)
   const int nw = dtype == NEDF_BF16 ? 8 : 4;
-  // both kinds in one binning; the counters report the networks' items
-  stage_bin_write(k, s, ids, mlp_mask | sphere_mask, mlp_mask ? mlp_mask : sphere_mask, mlp_mask ? 32 * nw : 1);
-  if (sphere_mask) hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
+  // both kinds in one binning, unless the list may not hold the pixels of both
+  // (a composition's workspace may be as small as one kind needs); the
+  // counters report the networks' items
+  const int per = mlp_mask ? 32 * nw : 1;
+  if (mlp_mask && sphere_mask && k.capacity < k.n_rays) {
+    stage_bin_write(k, s, ids, sphere_mask, sphere_mask, 1);
+    hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
+    stage_bin_write(k, s, ids, mlp_mask, mlp_mask, per);
+  } else {
+    stage_bin_write(k, s, ids, mlp_mask | sphere_mask, mlp_mask ? mlp_mask : sphere_mask, per);
+    if (sphere_mask) hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
+  }
   if (mlp_mask) {
     const Kernels kn = choose_kernels(k, dtype, 32, 3 * cu_count(), std::min<int64_t>(k.capacity, k.n_rays));
     if (kn.small) launch_refine_small(k, s, dtype, cu_count());
