@@ -248,9 +248,12 @@ __global__ __launch_bounds__(64 * NW, 1) void k_nedf_cls(KArgs a) {
 
 void launch_nedf_cls(const KArgs& k0, hipStream_t s, int dtype, int64_t bound) {
   KArgs k = k0;
-  const Kernels kn = choose_kernels(k, dtype, 128, cu_count(), bound);
-  if (dtype == NEDF_F32) hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(cu_count()), dim3(256), 0, s, k);
-  else if (kn.small) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+  if (dtype == NEDF_F32) {
+    hipLaunchKernelGGL((k_nedf_cls<0, 4>), dim3(cu_count()), dim3(256), 0, s, k);
+    return;
+  }
+  const Kernels kn = choose_kernels(k, 128, cu_count(), bound);
+  if (kn.small) hipLaunchKernelGGL((k_nedf_cls<1, 4>), dim3(cu_count()), dim3(256), 0, s, k);
   if (kn.large) hipLaunchKernelGGL((k_nedf_cls<1, 8>), dim3(cu_count()), dim3(512), 0, s, k);
 }
 

@@ -734,9 +734,8 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
-Kernels choose_kernels(KArgs& k, int dtype, int per, int most, int64_t bound) {
+Kernels choose_kernels(KArgs& k, int per, int most, int64_t bound) {
   k.split_per = 0;
-  if (dtype == NEDF_F32) return {true, false};
   if ((bound + per - 1) / per + k.n_obj <= most) return {true, false};
   k.split_per = per;
   k.split_max = most;
@@ -833,7 +832,7 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   if (W > 0) {
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, true);
     Kernels kn{false, true};
-    if (W == 256) kn = choose_kernels(k, dtype, 1, 4 * cu_count(), pair_bound(k));
+    if (W == 256) kn = dtype == NEDF_F32 ? Kernels{true, false} : choose_kernels(k, 1, 4 * cu_count(), pair_bound(k));
     if (kn.small) launch_march_small(k, s, dtype, cu_count());
     if (kn.large) launch_march(k, s, dtype, W);
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, false);
@@ -874,8 +873,8 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, S
     if (classifier) launch_nedf_cls(k, s, dtype, pair_bound(k));
     else {
       Kernels kn{false, true};
-      if (dtype == NEDF_F32 || (dtype == NEDF_BF16 && slabs.n == 1))
-        kn = choose_kernels(k, dtype, 32, 3 * cu_count(), pair_bound(k));
+      if (dtype == NEDF_F32) kn = choose_kernels(k, 32, 36 * cu_count(), pair_bound(k));
+      else if (dtype == NEDF_BF16 && slabs.n == 1) kn = choose_kernels(k, 32, 3 * cu_count(), pair_bound(k));
       if (kn.small) launch_nedf_small(k, s, dtype, cu_count());
       if (kn.large) launch_nedf(k, s, dtype, v);
     }

@@ -1,6 +1,6 @@
 // The NeDF intersection network (Eq. 1, 2, 7) in its regression form, with
-// routing of uncertain pairs to the marcher: BF16, FP8 and MX FP8 (FP32 lists
-// of any length run on the feature-split kernel).
+// routing of uncertain pairs to the marcher (short BF16 and FP32 lists run on
+// the feature-split kernel).
 #include "pipeline.h"
 #include "runtime.h"
 
@@ -126,6 +126,8 @@ void launch_nedf_net(const KArgs& k, hipStream_t s, int v) {
     // MX: superchunks of four blocks; eight waves (items of 256 pairs) or four
     if (v >= 1000) hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 8>), g1, b8, 0, s, k);
     else hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 4, 1, 1, 4>), g1, b4, 0, s, k);
+  } else {
+    hipLaunchKernelGGL((k_nedf<DT, 256, 8, 8, 1, 1, 1, 4>), g1, b4, 0, s, k);
   }
 }
 
@@ -134,7 +136,8 @@ void launch_nedf_net(const KArgs& k, hipStream_t s, int v) {
 void launch_nedf(const KArgs& k, hipStream_t s, int dtype, int v) {
   if (dtype == NEDF_FP8) launch_nedf_net<2>(k, s, v);
   else if (dtype == NEDF_FP8_MX) launch_nedf_net<3>(k, s, v);
-  else launch_nedf_net<1>(k, s, v);
+  else if (dtype == NEDF_BF16) launch_nedf_net<1>(k, s, v);
+  else launch_nedf_net<0>(k, s, v);
 }
 
 }  // namespace nedf

@@ -451,7 +451,8 @@ void stage_refine(const KArgs& k0, hipStream_t s, const int32_t* ids, uint32_t m
     if (sphere_mask) hipLaunchKernelGGL(k_refine_analytic, dim3(256), dim3(256), 0, s, k, sphere_mask);
   }
   if (mlp_mask) {
-    const Kernels kn = choose_kernels(k, dtype, 32, 3 * cu_count(), std::min<int64_t>(k.capacity, k.n_rays));
+    Kernels kn{true, false};
+    if (dtype == NEDF_BF16) kn = choose_kernels(k, 32, 3 * cu_count(), std::min<int64_t>(k.capacity, k.n_rays));
     if (kn.small) launch_refine_small(k, s, dtype, cu_count());
     if (kn.large)
       hipLaunchKernelGGL((k_refine_mlp<1, 256, 8, 10, 2, 1, 8>), dim3(cu_count()), dim3(512), 0, s, k);

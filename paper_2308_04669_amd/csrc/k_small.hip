@@ -1,16 +1,17 @@
 // The network stages on the feature-split engine: the intersection network,
 // the MLP marcher and the secant refinement of 256-wide, eight-layer
 // networks, for BF16 lists that leave the register-resident kernels short of
-// work and for every FP32 list.  One workgroup of eight waves evaluates 32
-// (or, per pass, 64) samples.
+// work, the network's FP32 lists up to 36 rounds, and every marched or refined
+// FP32 list.  One workgroup of eight waves evaluates 32 (or, per pass, 64)
+// samples.
 //
 // BF16: a pass is bound by the 1 MB of weights a compute unit reads from L2
 // (about 7 us at 64 bytes a clock); 32 pairs take 9-10 us against 31 us for
 // the 256 of a register-resident workgroup, so short lists end sooner and
-// long ones do not.  FP32: a pass is bound by the matrix cores in both forms
-// (73 us for 32 pairs, 257 us for the 128 of a register-resident workgroup of
-// four waves, whose one wave per SIMD waits at every barrier): the split form
-// has the higher rate and four times finer items.  Measured, before and after:
+// long ones do not.  FP32: a pass is bound by the matrix cores in both forms (69
+// us for 32 pairs, 261 us for the 128 of a register-resident workgroup of four
+// waves): the split form has four times finer items, and per 64 samples, two
+// blocks to a weight read, the higher rate too.  Measured, before and after:
 // 64 x 64 frame, 8 instances, BF16: march 155 -> 43 us, refinement 157 -> 46
 // us, network 31 -> 23 us; 20,011 FP32 rays, 24 instances: network 514 -> 366
 // us, march 992 -> 249 us, refinement 1,053 -> 522 us; FP32 marcher, 160 x

@@ -98,11 +98,15 @@ void launch_march_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid)
 void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid);
 
 // Sets up k for the choice between a stage's two kernels and says which to
-// launch: BF16 lists of at most `most` units of `per` pairs go to the small
-// one, FP32 lists always.  `most` is where the two take equal time: three
-// rounds of 32-pair units on the chip (3 x 10 us against 31 us for the one
-// round of the large kernel), four rounds of marched pairs (4 x 40 us against
-// its 4 serial passes of 38 us).
+// launch: lists of at most `most` units of `per` pairs go to the small one.
+// `most` is where the two take equal time: three rounds of 32-pair units on the
+// chip (3 x 10 us against 31 us for the one round of the large kernel), four
+// rounds of marched pairs (4 x 40 us against its 4 serial passes of 38 us).  In
+// FP32 a round of 32-pair units takes 69 us and one of the large network
+// kernel, four times the pairs, 261 us: it makes up for a part-empty last
+// round after some 36 rounds of the small one (2.17 M pairs: 18.3 ms on the
+// small kernel, 17.4 ms on the large one); the FP32 marcher and refinement
+// have the small kernels only, which are the faster at every length.
 // `bound` is the host's bound on the pairs; if it does not decide, both are
 // launched and the device's counts decide (the other ends at once, about
 // 4 us).  That holds for large calls too: a small object in a frame of 1.1 M
@@ -111,7 +115,7 @@ void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid
 struct Kernels {
   bool small, large;
 };
-Kernels choose_kernels(KArgs& k, int dtype, int per, int most, int64_t bound);
+Kernels choose_kernels(KArgs& k, int per, int most, int64_t bound);
 
 // Matrix-core marcher over the list in k (objects in its item_mask).
 void launch_march(const KArgs& k, hipStream_t s, int dtype, int W);
