@@ -34,7 +34,7 @@ def _scene(dtype, cls=False):
 
 
 @pytest.mark.parametrize("n", [33, 257])
-@pytest.mark.parametrize("stage", ["net_f32"])
+@pytest.mark.parametrize("stage", ["march", "refine", "net", "net_cls", "net_f32"])
 def test_both_kernels_of_a_stage_same_bits(stage, n):
     need_gpu()
     dtype = "f32" if stage == "net_f32" else "bf16"

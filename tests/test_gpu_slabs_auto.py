@@ -74,3 +74,18 @@ def test_slabs_do_not_depend_on_the_workspace():
     log(f"[auto slabs] {culled} culled pairs: {e0} evaluated, {e1} in the tight workspace")
     assert e0 < culled  # several slabs
     assert e0 == e1 and torch.equal(d0, d1) and torch.equal(i0, i1)
+
+
+@pytest.mark.parametrize("cls", [False, True])
+def test_slabs_of_long_lists_same_bits(cls):
+    """More than 8.4 M culled pairs: every wave of the slab filters takes
+    several blocks of 1,024 pairs and carries candidates from one to the next."""
+    need_gpu()
+    import torch
+    sc, cam = _stack(32, 1280, 720, cls=cls)
+    d1, i1, culled, e1 = _run(sc, cam, slabs=1)
+    assert culled > 8.4e6 and e1 == culled
+    for v in (2, 4, 32):
+        d, i, _, e = _run(sc, cam, slabs=v)
+        log(f"[long slabs] {v} slabs: {e} of {culled} pairs evaluated")
+        assert e < e1 and torch.equal(d, d1) and torch.equal(i, i1)
