@@ -832,7 +832,9 @@ void stage_march(const KArgs& k0, hipStream_t s, bool list_b, uint32_t analytic_
   if (W > 0) {
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, true);
     Kernels kn{false, true};
-    if (W == 256) kn = dtype == NEDF_F32 ? Kernels{true, false} : choose_kernels(k, 1, 4 * cu_count(), pair_bound(k));
+    if (W == 256 && dtype == NEDF_BF16) kn = choose_kernels(k, 1, 4 * cu_count(), pair_bound(k));
+    else if (W == 256 && k.n_samples <= 32) kn = choose_kernels(k, 1, 36 * cu_count(), pair_bound(k));
+    else if (W == 256) kn = {true, false};
     if (kn.small) launch_march_small(k, s, dtype, cu_count());
     if (kn.large) launch_march(k, s, dtype, W);
     prof_mark(list_b ? "fallback.mlp" : "march.mlp", s, false);

@@ -1,6 +1,6 @@
-// The plain volume-rendering marcher (Eq. 5) on MLP density fields: BF16, and
-// the 64-wide FP32 network (256-wide FP32 lists of any length run on the
-// feature-split kernel).
+// The plain volume-rendering marcher (Eq. 5) on MLP density fields (short BF16
+// lists and most FP32 lists of 256-wide networks run on the feature-split
+// kernel).
 #include "pipeline.h"
 #include "runtime.h"
 
@@ -129,7 +129,8 @@ void launch_march(const KArgs& k, hipStream_t s, int dtype, int W) {
     if (W == 256) launch_march_mlp<1, 256, 8, 10>(k, s);
     else launch_march_mlp<1, 64, 3, 6>(k, s);
   } else {
-    launch_march_mlp<0, 64, 3, 6>(k, s);
+    if (W == 256) launch_march_mlp<0, 256, 8, 10>(k, s);
+    else launch_march_mlp<0, 64, 3, 6>(k, s);
   }
 }
 

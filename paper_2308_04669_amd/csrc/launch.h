@@ -105,8 +105,10 @@ void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid
 // FP32 a round of 32-pair units takes 69 us and one of the large network
 // kernel, four times the pairs, 261 us: it makes up for a part-empty last
 // round after some 36 rounds of the small one (2.17 M pairs: 18.3 ms on the
-// small kernel, 17.4 ms on the large one); the FP32 marcher and refinement
-// have the small kernels only, which are the faster at every length.
+// small kernel, 17.4 ms on the large one), and so does the marcher with pairs
+// of at most 32 samples (25,600 rays, 16 objects: 3.6 and 3.4 ms).  With more
+// samples, and in the refinement, the small FP32 kernels take 64 samples to a
+// weight read and are the faster at every length.
 // `bound` is the host's bound on the pairs; if it does not decide, both are
 // launched and the device's counts decide (the other ends at once, about
 // 4 us).  That holds for large calls too: a small object in a frame of 1.1 M

@@ -43,6 +43,38 @@ def test_march_same_bits_in_every_pass(dtype, forms):
             assert np.array_equal(a, b), (samples, t_near)
 
 
+@pytest.mark.parametrize("samples", [1, 20, 32])
+def test_long_f32_lists_of_few_samples_same_bits(samples):
+    """Long lists of at most 32 samples take another kernel than short ones."""
+    need_gpu()
+    import torch
+    from paper_2308_04669_amd import api
+    models, insts, _, _ = syn.config2_scene(n_objects=3)
+    sc = gpu_scene(models, insts, "f32")
+    g = np.random.default_rng(8)
+    n = 250
+    o = np.concatenate([g.uniform(-1.0, 1.0, (n, 2)), np.full((n, 1), 13.0)], axis=1).astype(np.float32)
+    t = np.concatenate([g.uniform(-3.0, 3.0, (n, 2)), np.zeros((n, 1))], axis=1)
+    d = ((t - o) / np.linalg.norm(t - o, axis=1, keepdims=True)).astype(np.float32)
+    limit = 36 * torch.cuda.get_device_properties(0).multi_processor_count
+
+    def run(o, d):
+        ws = api.Workspace()
+        rays = api.array_rays(torch.from_numpy(o).cuda(), torch.from_numpy(d).cuda())
+        out = api.march_depth(sc, rays, n_samples=samples, dtype="f32", ws=ws)
+        torch.cuda.synchronize()
+        return [x.cpu().numpy().view(np.uint32) for x in out], api.ws_counters(ws)["pairs"]
+
+    one, p1 = run(o, d)
+    copies = -(-2 * limit // p1)
+    many, pn = run(np.tile(o, (copies, 1)), np.tile(d, (copies, 1)))
+    log(f"[march lists] f32, {samples} samples: {p1} and {pn} pairs about the limit {limit}, "
+        f"opacity up to {one[2].view(np.float32).max():.3f}")
+    assert 0 < p1 <= limit - len(models) and pn > limit
+    for a, b in zip(one, many):
+        assert np.array_equal(np.tile(a, copies), b)
+
+
 def test_march_f32_time_follows_the_samples():
     """32 samples cost about half of 64, 96 about three quarters of 128."""
     need_gpu()
