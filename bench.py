@@ -75,7 +75,8 @@ TRAFFIC_RECORDS = {
     "train.step": os.path.join(ROOT, "profiles", "train_step_bf16_65536rays.md"),
 }
 TRAIN_SOURCES = ["include/nedf.h"] + ["paper_2308_04669_amd/csrc/" + f for f in (
-    "k_train.hip", "k_chain.hip", "train_engine.h", "train_kernels.h", "train_layout.h", "mlp_engine.h")]
+    "k_train.hip", "k_chain.hip", "train_engine.h", "train_kernels.h", "train_layout.h", "mlp_engine.h",
+    "device_common.h", "blob_layout.h")]
 
 
 def sources_hash(files) -> str:

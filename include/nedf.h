@@ -492,10 +492,11 @@ int32_t nedf_fp8_calibrate(const nedf_mlp_shape* shape, const float* const* W, c
  * runs the intersection network front to back (1, 2, 4, 8, 16 or 32; an exact
  * pruning: a pair whose smallest possible depth lies beyond the pixel's
  * nearest hit is skipped).  Its initial value, 0, leaves the number to the
- * library, which chooses by rays x instances of the call; 0 is not among the
- * candidates, but nedf_tune_set takes it to restore that state.  The values
- * are kept per kernel and dtype in a process-wide table guarded by a mutex
- * (the library's only global state besides the profiler).
+ * library, which chooses by rays x instances of the call and the pairs left
+ * after culling; 0 is not among the candidates, but nedf_tune_set takes it to
+ * restore that state.  The values are kept per kernel and dtype in a
+ * process-wide table guarded by a mutex (the library's only global state
+ * besides the profiler).
  *
  * nedf_tune_candidates writes the values instantiated for (kernel, dtype) into
  * out (up to NEDF_TUNE_MAX) and their number into n.  nedf_tune_get/nedf_tune_set read and

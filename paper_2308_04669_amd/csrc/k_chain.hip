@@ -36,7 +36,7 @@ __device__ __forceinline__ float from_hi(float x) {
 // 65,536 rows and 8 layers, 130 GFLOP at 1.1 PFLOP/s) and by the writes of
 // the layers' inputs and gradients (15 x 33.6 MB + 16.8 MB): 158 us with
 // both.  One launch per layer and direction took 300 us for the same work
-// (each read its input back), the step 473 us against 333 us now.  The ring,
+// (each read its input back), the step 473 us against 318 us now.  The ring,
 // the biases and the head weights in LDS allow one workgroup per compute
 // unit; 8 waves keep two on each SIMD, 4 serve the batches that would leave
 // compute units without a workgroup (chain_line_waves).

@@ -847,7 +847,7 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, S
   k.item_mask = nedf_mask;
   k.loff = k.C->A.off;
   // launch shape from the tuning table, fixed for all slabs of the stage
-  int v = dtype == NEDF_F32 ? 11 : dtype == NEDF_FP8_MX ? 1014 : tune_value(NEDF_TUNE_NEDF, dtype);
+  int v = dtype == NEDF_FP8_MX ? 1014 : tune_value(NEDF_TUNE_NEDF, dtype);
   // FP8: eight waves (1.94 against 1.18 PFLOP/s with four, one per SIMD: the
   // quantising epilogues lie under the other wave's products) unless the call
   // is sure to fit one round of 128-pair items, which four waves finish in

@@ -7,8 +7,8 @@
 namespace nedf {
 namespace {
 
-// Matrix-core marcher: a workgroup takes items of 4 pairs (one per wave) of
-// one object from list a.L; each wave marches its pair in chunks of 32 NB
+// Matrix-core marcher: a workgroup takes items of NW pairs (one per wave) of
+// one object of the list; each wave marches its pair in chunks of 32 NB
 // samples through the register-resident density network (NB blocks of 32
 // share every weight read from LDS), then scans each block's optical depths
 // across the wave in sample order, so that the sums are the same for any NB.

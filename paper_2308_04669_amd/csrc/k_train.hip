@@ -263,7 +263,7 @@ struct WgradProb {
 };
 struct WgradBatch {
   WgradProb p[NEDF_TRAIN_MAX_LAYERS];
-  int n, S, M, B;
+  int S, M, B;
 };
 constexpr int WG_TILE = 128;                  // rows and columns of a workgroup's tile
 constexpr int WG_SLOT = 2 * WG_TILE * 32 * 2;  // bytes of a stage: 32 samples of both operands
@@ -633,10 +633,10 @@ __global__ void k_train_encode_points(const float* o_l, const float* d_l, const 
 }  // namespace
 
 // Split count of a batched weight-gradient launch over `tiles` 128 x 128
-// output tiles: a power of two up to 64 giving at most 640 workgroups (two
-// per compute unit and a quarter more, so that the last wave of workgroups
-// is short), with the batch a multiple of 128 per split (the batch is a
-// multiple of 256).
+// output tiles: a power of two up to 64 giving at most 640 workgroups, one
+// round (three share a compute unit, 768 in all; a second round would be part
+// empty, and every split's partial sums are written and read back), with the
+// batch a multiple of 128 per split (the batch is a multiple of 256).
 int wgrad_batch_splits(int B, int tiles) {
   int S = 1;
   while (S < 64 && tiles * S * 2 <= 640 && B % (S * 2 * 128) == 0) S *= 2;
@@ -754,7 +754,7 @@ hipError_t launch_train_step(const nedf_mlp_shape& sh, uint8_t* st, const float*
   // launch, then their sums over the splits in order
   {
     WgradBatch wb{};
-    wb.n = NH; wb.S = S; wb.M = W; wb.B = B;
+    wb.S = S; wb.M = W; wb.B = B;
     ReduceArgs ra{};
     ra.n_layers = NH;
     ra.S = S;
@@ -880,7 +880,7 @@ hipError_t launch_train_step_cls(const nedf_mlp_shape& sh, uint8_t* st, const fl
   // input, in one launch, then their sums over the splits in order
   {
     WgradBatch wb{};
-    wb.n = tl.n_layers; wb.S = S; wb.M = W; wb.B = B;
+    wb.S = S; wb.M = W; wb.B = B;
     ReduceArgs ra{};
     ra.n_layers = tl.n_layers;
     ra.S = S;
