@@ -61,10 +61,11 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_nedf_small(KArgs a) {
   if (threadIdx.x < 64) flush_routing(a, lane, n_route);
 }
 
-// Marcher: a workgroup takes one pair at a time, 64 samples per pass and the
-// last 32 or fewer in a pass of their own (FP32, 160 x 160 rays, 16 objects, 32
-// samples: 6.3 ms with half of every pass empty, 3.6 without).
-template <int DT>
+// Marcher: a workgroup takes one pair at a time, 64 samples per pass; with
+// TAIL the last 32 or fewer take a pass of their own (FP32, 160 x 160 rays, 16
+// objects, 32 samples: 6.3 ms with half of every pass empty, 3.6 without).  An
+// instantiation of its own, since its code costs the others 1 %.
+template <int DT, bool TAIL>
 __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
   constexpr int L = 10, KS0 = eng::ks_for_slots<DT>(3 * L + 2);
   __shared__ __attribute__((aligned(16))) uint8_t lds[coop::Lds<DT, 2, 1>::BYTES];
@@ -116,8 +117,8 @@ __global__ __launch_bounds__(coop::THREADS, 1) void k_march_small(KArgs a) {
       }
     };
     int s0 = 0;
-    for (; N - s0 > 32; s0 += 64) pass(std::integral_constant<int, 2>{}, s0);
-    if (s0 < N) pass(std::integral_constant<int, 1>{}, s0);
+    for (; N - s0 > (TAIL ? 32 : 0); s0 += 64) pass(std::integral_constant<int, 2>{}, s0);
+    if constexpr (TAIL) pass(std::integral_constant<int, 1>{}, s0);
     if (threadIdx.x == 0) sum.emit(a, pr, g.s);
   }
 }
@@ -189,8 +190,15 @@ void launch_nedf_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) 
 }
 
 void launch_march_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) {
-  if (dtype == NEDF_BF16) hipLaunchKernelGGL(k_march_small<1>, dim3(grid), dim3(coop::THREADS), 0, s, k);
-  else hipLaunchKernelGGL(k_march_small<0>, dim3(grid), dim3(coop::THREADS), 0, s, k);
+  const dim3 g(grid), b(coop::THREADS);
+  const bool tail = (k.n_samples - 1) % 64 < 32;  // 1 to 32 samples beyond whole passes
+  if (dtype == NEDF_BF16) {
+    if (tail) hipLaunchKernelGGL((k_march_small<1, true>), g, b, 0, s, k);
+    else hipLaunchKernelGGL((k_march_small<1, false>), g, b, 0, s, k);
+  } else {
+    if (tail) hipLaunchKernelGGL((k_march_small<0, true>), g, b, 0, s, k);
+    else hipLaunchKernelGGL((k_march_small<0, false>), g, b, 0, s, k);
+  }
 }
 
 void launch_refine_small(const KArgs& k, hipStream_t s, int dtype, unsigned grid) {
