@@ -860,6 +860,11 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, S
   bool others = k.ray_tmax != nullptr;
   for (int m = 0; m < k.n_obj; ++m) others |= !((nedf_mask >> m) & 1u);
   const bool direct = slabs.n == 1 && !(others && pair_bound(k) > (1 << 20));
+  // FP32: the kernel of long lists (choose_kernels) gains 5 % where it runs and
+  // costs a launch per slab where it does not, so it is launched only if even an
+  // even share of rays x instances makes a slab twice as long as it needs
+  const int f32_units = 36 * cu_count();
+  const bool f32_large = pair_bound(k) / slabs.n > 2 * 32 * int64_t(f32_units);
   for (int slab = 0; slab < slabs.n; ++slab) {
     if (direct) {
       k.lcnt = k.C->A.cnt;
@@ -875,7 +880,7 @@ void stage_nedf(const KArgs& k0, hipStream_t s, int dtype, uint32_t nedf_mask, S
     if (classifier) launch_nedf_cls(k, s, dtype, pair_bound(k));
     else {
       Kernels kn{false, true};
-      if (dtype == NEDF_F32) kn = choose_kernels(k, 32, 36 * cu_count(), pair_bound(k));
+      if (dtype == NEDF_F32) kn = f32_large ? choose_kernels(k, 32, f32_units, pair_bound(k)) : Kernels{true, false};
       else if (dtype == NEDF_BF16 && slabs.n == 1) kn = choose_kernels(k, 32, 3 * cu_count(), pair_bound(k));
       if (kn.small) launch_nedf_small(k, s, dtype, cu_count());
       if (kn.large) launch_nedf(k, s, dtype, v);

@@ -26,6 +26,17 @@ def _query(sc, o, d, dtype, **kw):
     return dep.cpu().numpy().view(np.uint32), idn.cpu().numpy(), api.ws_counters(ws)
 
 
+def _query_one_slab(sc, o, d, dtype, **kw):
+    """All pairs in one list of the network stage."""
+    from paper_2308_04669_amd import api
+    old = api.tune_get("slabs", dtype)
+    try:
+        api.tune_set("slabs", dtype, 1)
+        return _query(sc, o, d, dtype, **kw)
+    finally:
+        api.tune_set("slabs", dtype, old)
+
+
 def _scene(dtype, cls=False):
     models, insts, _ = syn.sdf_scene(3, 6)
     nets = [syn.classifier_model(3, 500 + k, n_blocks=2, bias_std=0.05) if cls else syn.nedf_model(3, 200 + k)
@@ -51,9 +62,10 @@ def test_both_kernels_of_a_stage_same_bits(stage, n):
     def listed(st):
         return {"march": st["fallback_marched"], "refine": st["pairs"]}.get(stage, st["culled_pairs"])
 
-    d1, i1, st1 = _query(sc, o, d, dtype, **kw)
+    query = _query_one_slab if stage.startswith("net") else _query
+    d1, i1, st1 = query(sc, o, d, dtype, **kw)
     copies = -(-2 * most // max(1, listed(st1)))
-    dn, idn, stn = _query(sc, np.tile(o, (copies, 1)), np.tile(d, (copies, 1)), dtype, **kw)
+    dn, idn, stn = query(sc, np.tile(o, (copies, 1)), np.tile(d, (copies, 1)), dtype, **kw)
     log(f"[list routes] {stage}, {n} rays: {listed(st1)} and {listed(stn)} pairs about the limit {most}")
     assert 0 < listed(st1) <= most - unit * n_obj and listed(stn) > most
     if stage.startswith("net"):
